@@ -156,8 +156,8 @@ int amg_p1_assemble(int dim, int32_t nv, const double *coords, int32_t ne, const
                     double *valA, double *valM);
 
 /* ---- The same assembly on the GPU (Section 2), bit-identical to amg_p1_assemble:
- *      one thread per row adds the row vertex's element contributions in ascending
- *      element index with the host's element arithmetic (no fused multiply-add). ----
+ *      every entry adds its elements' contributions in ascending element index with
+ *      the host's element arithmetic (no fused multiply-add). ----
  * amg_p1_pattern_device: *nnz (host) = stored entries of the mesh graph.
  *   elems: device int32 [ne x (dim+1)].
  * amg_p1_assemble_device: device outputs rowptr[nv+1], col[nnz], valA[nnz], valM[nnz]
@@ -179,6 +179,22 @@ int amg_p1_assemble_device(int dim, int32_t nv, const double *coords, int32_t ne
                            const int32_t *elems, const double *kappa, int32_t nnz,
                            int32_t *rowptr, int32_t *col, double *valA, double *valM,
                            void *stream);
+
+/* The same in two steps that share the mesh's lists (the two calls above each build
+ * them): amg_p1_plan_device builds them, returns *nnz (host) and a plan that holds them;
+ * amg_p1_assemble_planned fills the caller's arrays from it, as often as the caller
+ * likes (new coordinates or coefficients on the same elements), on the plan's stream.
+ * elems must hold what it held when the plan was made.  amg_p1_plan_destroy ends the
+ * plan, whose memory (about 4 (3 nv + ne (dim+1)) bytes) goes back to the library's
+ * cache; NULL is accepted.  Results and errors are those of amg_p1_assemble_device;
+ * on error *plan is NULL. */
+typedef struct amg_p1_plan amg_p1_plan;
+int amg_p1_plan_device(int dim, int32_t nv, int32_t ne, const int32_t *elems, int32_t *nnz,
+                       void *stream, amg_p1_plan **plan);
+int amg_p1_assemble_planned(amg_p1_plan *plan, const double *coords, const int32_t *elems,
+                            const double *kappa, int32_t *rowptr, int32_t *col, double *valA,
+                            double *valM);
+int amg_p1_plan_destroy(amg_p1_plan *plan);
 
 /* amg_p1_assemble_device without any device allocation, for callers that cannot
  * allocate (code that runs between graph captures or inside a serving loop, or a

@@ -40,7 +40,7 @@ def assemble_p1(coords: np.ndarray, elems: np.ndarray, kappa: np.ndarray):
 
 
 def assemble_p1_device(coords, elems, kappa):
-    """The same assembly on the GPU (amg_p1_pattern_device / amg_p1_assemble_device),
+    """The same assembly on the GPU (amg_p1_plan_device / amg_p1_assemble_planned),
     bit-identical to assemble_p1.  coords (nv x dim, float64), elems (ne x (dim+1),
     int32) and kappa (ne, float64) are CUDA tensors; returns CUDA tensors (rowptr,
     col, valA, valM), computed on torch's current stream."""
@@ -57,14 +57,18 @@ def assemble_p1_device(coords, elems, kappa):
     L = lib()
     stream = C.c_void_p(torch.cuda.current_stream(coords.device).cuda_stream)
     nnz = C.c_int32(0)
-    check(L.amg_p1_pattern_device(dim, nv, ne, elems.data_ptr(), C.byref(nnz), stream))
-    dev = coords.device
-    rowptr = torch.empty(nv + 1, dtype=torch.int32, device=dev)
-    col = torch.empty(nnz.value, dtype=torch.int32, device=dev)
-    valA = torch.empty(nnz.value, dtype=torch.float64, device=dev)
-    valM = torch.empty(nnz.value, dtype=torch.float64, device=dev)
-    check(L.amg_p1_assemble_device(dim, nv, coords.data_ptr(), ne, elems.data_ptr(), kappa.data_ptr(), nnz.value,
-                                   rowptr.data_ptr(), col.data_ptr(), valA.data_ptr(), valM.data_ptr(), stream))
+    plan = C.c_void_p()
+    check(L.amg_p1_plan_device(dim, nv, ne, elems.data_ptr(), C.byref(nnz), stream, C.byref(plan)))
+    try:
+        dev = coords.device
+        rowptr = torch.empty(nv + 1, dtype=torch.int32, device=dev)
+        col = torch.empty(nnz.value, dtype=torch.int32, device=dev)
+        valA = torch.empty(nnz.value, dtype=torch.float64, device=dev)
+        valM = torch.empty(nnz.value, dtype=torch.float64, device=dev)
+        check(L.amg_p1_assemble_planned(plan, coords.data_ptr(), elems.data_ptr(), kappa.data_ptr(),
+                                        rowptr.data_ptr(), col.data_ptr(), valA.data_ptr(), valM.data_ptr()))
+    finally:
+        L.amg_p1_plan_destroy(plan)
     return rowptr, col, valA, valM
 
 

@@ -83,3 +83,38 @@ def test_device_assembly_rejects_bad_input():
     n = C.c_int32(0)
     assert L.amg_p1_pattern_device(4, m.nverts, len(m.elems), elems.data_ptr(), C.byref(n), None) == -1
     assert L.amg_p1_pattern_device(2, m.nverts, len(m.elems), None, C.byref(n), None) == -1
+
+
+def ring_mesh(dim, k, degenerate=False):
+    # k simplices around one vertex (2D) or one edge (3D), whose rows then have k
+    # elements and k + 1 or k + 2 entries, on vertices numbered at random
+    rng = np.random.default_rng(100 * dim + k)
+    t = 2.0 * np.pi * np.arange(k) / k
+    ring = np.stack([np.cos(t), np.sin(t)] + [0.1 * np.sin(3 * t)] * (dim - 2), axis=1)
+    hub = np.zeros((1, 2)) if dim == 2 else np.array([[0.0, 0.0, -1.0], [0.0, 0.0, 1.0]])
+    h = len(hub)
+    nxt = (np.arange(k) + 1) % k
+    elems = np.stack([np.full(k, a) for a in range(h)] + [h + np.arange(k), h + nxt], axis=1)
+    if degenerate:  # an element that holds a vertex twice
+        elems[k // 2, -1] = elems[k // 2, -2]
+    perm = rng.permutation(h + k)
+    coords = np.empty((h + k, dim))
+    coords[perm] = np.concatenate([hub, ring]) + 0.01 * rng.standard_normal((h + k, dim))
+    return coords, perm[elems[rng.permutation(k)]].astype(np.int32), rng.uniform(0.5, 2.0, k)
+
+
+# around the limits of the row kernels: 32 and 64 elements per row, 127 entries
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("k", [3, 31, 32, 33, 63, 64, 65, 124, 125, 126, 127, 128, 300])
+@pytest.mark.parametrize("degenerate", [False, True])
+def test_rows_at_the_limits_of_the_row_kernels(dim, k, degenerate):
+    _need_gpu()
+    import paper_2001_11533_amd as amg
+    print(f"[assembly] ring dim={dim} k={k} degenerate={degenerate}", flush=True)
+    coords, elems, kappa = ring_mesh(dim, k, degenerate)
+    with np.errstate(all="ignore"):
+        ref = amg.assemble_p1(coords, elems, kappa)
+    got = [x.cpu().numpy() for x in amg.assemble_p1_device(dev(coords, torch.float64), dev(elems, torch.int32),
+                                                           dev(kappa, torch.float64))]
+    for a, b in zip(got, ref):
+        assert np.array_equal(a, b, equal_nan=a.dtype == np.float64)
