@@ -241,9 +241,13 @@ __global__ __launch_bounds__(kAsmBlock) void k_row_count(int32_t nv, const int32
 // bytes (the row vertex's own place marked by the top bit), and the lanes turn
 // to the row's entries: an entry walks the elements in order and adds the
 // contributions whose position byte is its own, in registers.  Bound by
-// instruction issue (FP64 divisions of the gradients, four times per element,
-// and the walk).  One thread per row that added into global memory behind a
-// binary search took 2021 us at 64^3 for the values alone.
+// instruction issue and LDS latency at four wavefronts per SIMD (FP64 divisions
+// of the gradients, four times per element, the rankings and the walk): every
+// loop over a row's lists therefore reads LDS in 16-byte words, four entries or
+// elements at a time, and lists share storage where their uses end (2064 bytes
+// per row).  64^3: 235 us, 318 us with one entry per LDS read and 2816 bytes;
+// one thread per row that added into global memory behind a binary search took
+// 2021 us for the values alone.
 template <int DIM, int E>
 __global__ __launch_bounds__(kAsmBlock) void k_row_fill(int32_t nv, const double *__restrict__ coords,
                                                         const int32_t *__restrict__ elems,
@@ -254,16 +258,26 @@ __global__ __launch_bounds__(kAsmBlock) void k_row_fill(int32_t nv, const double
                                                         int32_t *__restrict__ col, double *__restrict__ valA,
                                                         double *__restrict__ valM) {
     constexpr int NL = DIM + 1, SLOTS = 4 * E, KP = E / kRowLanes;
+    constexpr int KEYS = (1 + E * DIM < kFillLen ? 1 + E * DIM : kFillLen) / 4 * 4 + 4;  // entries, in fours
     struct Row {
-        double s[E][NL];       // stiffness contributions, by element rank and place in the element
-        double m[E];           // mass contribution off the diagonal (the diagonal's is twice it)
-        int32_t tab[SLOTS];
-        int32_t key[kFillLen + 1];  // the distinct vertices in table order
-        int32_t se[E];
-        uint32_t pos[E];
-        uint8_t at[kFillLen + 1];   // their slots
-        uint8_t rk[SLOTS];          // slot -> position in the row
-        uint32_t pad[8];            // rows of a wavefront start in different banks
+        union {
+            int32_t tab[SLOTS];  // the distinct vertices; its keys are read out before s is written
+            double s[E][NL];     // stiffness contributions, by element rank and place in the element
+        };
+        double m[E];             // mass contribution off the diagonal (the diagonal's is twice it)
+        union {
+            int4 se4[E / 4];     // the elements, read out before key is written
+            int32_t se[E];
+            int4 key4[KEYS / 4]; // the distinct vertices in table order, then INT_MAX
+            int32_t key[KEYS];
+        };
+        union {
+            uint4 pos4[E / 4];
+            uint32_t pos[E];
+        };
+        uint8_t at[KEYS];        // the keys' slots
+        uint8_t rk[SLOTS];       // slot -> position in the row
+        uint32_t pad[4];         // rows of a wavefront start in different banks
     };
     static_assert(SLOTS <= 256, "slots are kept in a byte");
     __shared__ Row rows[kRowsPerBlock];
@@ -300,9 +314,14 @@ __global__ __launch_bounds__(kAsmBlock) void k_row_fill(int32_t nv, const double
             for (int b = 0; b < NL; ++b) slot[k][b] = 0;
             const int j = k * kRowLanes + g;
             if (j >= deg) continue;
-            for (int i = 0; i < deg; ++i) {  // an element that holds the vertex twice is listed twice
-                const int32_t x = R.se[i];
-                rank[k] += x < eid[k] || (x == eid[k] && i < j);
+            // an element that holds the vertex twice is listed twice; the list ends in INT_MAX
+#pragma unroll
+            for (int i = 0; i < E / 4; ++i) {
+                const int4 x = R.se4[i];
+                rank[k] += (x.x < eid[k] || (x.x == eid[k] && 4 * i < j)) +
+                           (x.y < eid[k] || (x.y == eid[k] && 4 * i + 1 < j)) +
+                           (x.z < eid[k] || (x.z == eid[k] && 4 * i + 2 < j)) +
+                           (x.w < eid[k] || (x.w == eid[k] && 4 * i + 3 < j));
             }
 #pragma unroll
             for (int b = 0; b < NL; ++b) {
@@ -326,16 +345,21 @@ __global__ __launch_bounds__(kAsmBlock) void k_row_fill(int32_t nv, const double
 #pragma unroll
             for (int i = 0; i < SLOTS / kRowLanes; ++i) {
                 const int32_t x = R.tab[i * kRowLanes + g];
-                if (x < 0 || o > kFillLen) continue;
+                if (x < 0 || o >= KEYS) continue;
                 R.key[o] = x;
                 R.at[o] = (uint8_t)(i * kRowLanes + g);
                 ++o;
             }
+        if (g < 4 && len + g < KEYS) R.key[len + g] = INT_MAX;  // the last four read may pass the row's end
         wave_sync();
         for (int i = g; i < len; i += kRowLanes) {
             const int32_t x = R.key[i];
             int q = 0;
-            for (int k = 0; k < len; ++k) q += R.key[k] < x;
+#pragma unroll 4
+            for (int k = 0; k < len; k += 4) {
+                const int4 y = R.key4[k / 4];
+                q += (y.x < x) + (y.y < x) + (y.z < x) + (y.w < x);
+            }
             R.rk[R.at[i]] = (uint8_t)q;
             col[r0 + q] = x;
         }
@@ -375,17 +399,33 @@ __global__ __launch_bounds__(kAsmBlock) void k_row_fill(int32_t nv, const double
         for (int q = g; q < len; q += kRowLanes) {
             double sA = 0.0, sM = 0.0;
             const uint32_t want = (uint32_t)q * 0x01010101u;
-            for (int j = 0; j < deg; ++j) {
-                const uint32_t pos = R.pos[j];
-                // the top bit of every byte of `hit` whose position is q (7-bit
-                // values: the sum does not carry from byte to byte)
-                uint32_t hit = ~(((pos & 0x7f7f7f7fu) ^ want) + 0x7f7f7f7fu) & 0x80808080u;
-                while (hit) {
-                    const int b = (__ffs(hit) - 1) >> 3;
-                    const double m = R.m[j];
-                    sA = sA + R.s[j][b];
-                    sM = sM + ((pos >> (8 * b)) & 0x80u ? 2.0 * m : m);
-                    hit &= hit - 1;
+            for (int j0 = 0; j0 < deg; j0 += 4) {  // four elements' contributions in flight
+                const uint4 p4 = R.pos4[j0 / 4];
+                const uint32_t pp[4] = {p4.x, p4.y, p4.z, p4.w};
+                uint32_t hit[4];
+                double cs[4], cm[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    // the top bit of every byte whose position is q (7-bit values: the
+                    // sum does not carry from byte to byte)
+                    hit[i] = ~(((pp[i] & 0x7f7f7f7fu) ^ want) + 0x7f7f7f7fu) & 0x80808080u;
+                    if (j0 + i >= deg) hit[i] = 0;
+                    const int b = hit[i] ? (__ffs(hit[i]) - 1) >> 3 : 0;
+                    cs[i] = R.s[j0 + i][b];
+                    const double m = R.m[j0 + i];
+                    cm[i] = (pp[i] >> (8 * b)) & 0x80u ? 2.0 * m : m;
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (!hit[i]) continue;
+                    sA = sA + cs[i];
+                    sM = sM + cm[i];
+                    for (uint32_t h = hit[i] & (hit[i] - 1); h; h &= h - 1) {  // a vertex held twice
+                        const int b = (__ffs(h) - 1) >> 3;
+                        const double m = R.m[j0 + i];
+                        sA = sA + R.s[j0 + i][b];
+                        sM = sM + ((pp[i] >> (8 * b)) & 0x80u ? 2.0 * m : m);
+                    }
                 }
             }
             valA[r0 + q] = sA;
