@@ -332,7 +332,7 @@ template <int NB> int tune_apply(Ctx &c) {
     for_tunables<NB>(c, [&](const char *kind, DCsr &A, int, int prec, bool) {
         const auto it = t.lg.find(tune_key(dev, kind, A, NB, prec));
         if (it == t.lg.end()) return;
-        A.tuned_lg[ilog2(NB)][prec == 32 ? 1 : 0] = (int8_t)it->second;
+        A.tuned_lg[ilog2(NB)][prec == 32 ? 1 : 0] = (int8_t)std::min(it->second, max_lg<NB>());
         ++n;
     });
     return n;
@@ -369,17 +369,8 @@ template <int NB> int tune_time(Ctx &c, int reps) {
             if (t.lg.count(key)) return;
         }
         const int pi = prec == 32 ? 1 : 0, nbi = ilog2(NB);
-        const int lgmax = is_t ? 6 - ilog2(NB) : max_lg<NB>();
-        // the default rule's choice
-        int lg_def;
-        if (is_t) {
-            const double mm = A.n > 0 ? (double)A.nnz / (double)A.n : 1.0;
-            int G = 1;
-            while (G * NB < 64 && G < mm / kSpmvUnroll) G <<= 1;
-            lg_def = ilog2(G);
-        } else {
-            lg_def = make_geo<NB>(A.nnz, A.n).lg;
-        }
+        const int lgmax = max_lg<NB>();
+        const int lg_def = make_geo<NB>(A.nnz, A.n, is_t && prec == 32).lg;  // the default rule's choice
         auto launch = [&](auto tT) {
             using T = decltype(tT);
             Level &Lv = c.lev[l];

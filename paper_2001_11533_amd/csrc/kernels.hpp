@@ -102,14 +102,30 @@ inline int ilog2(int x) {
 // entries a lane loads together
 constexpr int kSpmvUnroll = 4;
 
-// G = next power of two >= (mean entries per row) / U, at most 64 / (NB / CV)
-template <int NB> inline Geo make_geo(long nnz, long rows) {
+// The fixed rule for G, from the mean row length m (measured over G = 1 .. 64 on
+// every product of 2D and 3D hierarchies of 7e4 to 2.1e6 rows, 1 to 16 columns):
+//   one or two columns: enough lanes that a row takes one round of U loads,
+//     G = next power of two >= m / U; the float32 pass over T with U < m <= 2 U
+//     takes one step more (its rows spread up to twice the mean: 65 -> 41 us at
+//     2.1e6 rows, 10.7 -> 7.0 us at 2.7e5);
+//   more columns: a lane's U loads are already CV columns each, so a lane serves
+//     more entries, up to 6 (NB = 4), 8 (NB = 8) or 14 (NB = 16) of a row, but a
+//     row of more than U entries gets two lanes up to NB = 8 (16 columns at
+//     184344 rows of 33 entries: 33.6 us with G = 4, 39.2 us with m / U; the pass
+//     over T at 2.1e6 rows: 252 us with G = 1, 266 with 2, 313 with 4); and small
+//     matrices widen G, up to m / 2, until the launch has 2^17 lanes (16 columns
+//     at 1742 rows of 94 entries: 3.5 us with G = 16, 5.3 us with 4).
+template <int NB> inline Geo make_geo(long nnz, long rows, bool t32 = false) {
     constexpr int NG = NB / spmv_cv<NB>();
     const double m = rows > 0 ? (double)nnz / (double)rows : 1.0;
+    constexpr double per = NB <= 2 ? kSpmvUnroll : NB == 4 ? 6.0 : NB == 8 ? 8.0 : 14.0;
     int g = 1;
-    while (g < 64 && g < m / kSpmvUnroll) g <<= 1;
+    while (g < 64 && g < m / per) g <<= 1;
+    if (NB <= 8 && m > kSpmvUnroll) g = std::max(g, 2);
+    if (NB <= 4 && t32 && m > kSpmvUnroll && m <= 2 * kSpmvUnroll) g = 4;
+    if constexpr (NB > 2)
+        while (rows * NG * g < (1L << 17) && 4 * g <= m) g <<= 1;
     while (g * NG > 64) g >>= 1;
-    if (g < 1) g = 1;
     Geo geo;
     geo.lg = ilog2(g);
     geo.llpr = ilog2(g * NG);
@@ -127,10 +143,12 @@ template <int NB> inline Geo geo_from_lg(int lg) {
 // largest log2 G a product on NB columns can take (LPR <= 64)
 template <int NB> constexpr int max_lg() { return NB >= 4 ? 6 - (NB == 4 ? 0 : NB == 8 ? 1 : 2) : 6; }
 
-// the autotuner's choice for this matrix, batch width and value type, else the default rule
-template <int NB, typename T> inline Geo geo_for(const DCsr &A) {
-    const int t = A.tuned_lg[ilog2(NB)][std::is_same_v<T, float> ? 1 : 0];
-    return t >= 0 ? geo_from_lg<NB>(t) : make_geo<NB>(A.nnz, A.n);
+// the autotuner's choice for this matrix, batch width and value type, else the
+// default rule (is_t: the fused pass over T = A S)
+template <int NB, typename T> inline Geo geo_for(const DCsr &A, bool is_t = false) {
+    constexpr bool f32 = std::is_same_v<T, float>;
+    const int t = A.tuned_lg[ilog2(NB)][f32 ? 1 : 0];
+    return t >= 0 ? geo_from_lg<NB>(t) : make_geo<NB>(A.nnz, A.n, is_t && f32);
 }
 
 template <int NV, int NB> struct Reducer {
@@ -919,34 +937,43 @@ template <typename T, int NB, bool DOT> struct EPost {
 // whose pattern contains that of S), come from one pass over T's pattern that
 // carries S's values aligned to it (zero where S has no entry): per row i and
 // column c, se = (S e)_i and te = (T e)_i, both gathered from the coarse
-// vector e.  LPR = G NB lanes per row: G groups over the entries, one lane per
-// column; the epilogue receives both sums.  Columns are int32 or, when the
-// coarse level has at most 65536 nodes, 16-bit (CI = uint16_t).
+// vector e.  LPR = G NG lanes per row as in spmv_kernel: G groups over the
+// entries, NG groups of CV consecutive columns, so a gather of e is CV
+// contiguous values; the epilogue receives both sums.  Columns are int32 or,
+// when the coarse level has at most 65536 nodes, 16-bit (CI = uint16_t).
 template <typename T, int NB, int NV, class EP, typename CI = int>
 __global__ __launch_bounds__(kBlock) void tpro_kernel(int nrows, const int *__restrict__ rp,
                                                       const CI *__restrict__ ci, const T *__restrict__ tv,
                                                       const T *__restrict__ sv, const T *__restrict__ e, EP ep,
-                                                      int llpr, Reducer<(NV > 0 ? NV : 1), NB> red,
+                                                      Geo geo, Reducer<(NV > 0 ? NV : 1), NB> red,
                                                       const int *__restrict__ stop) {
     if (stop && *stop) return;
-    const int t = threadIdx.x, LPR = 1 << llpr, RPB = kBlock >> llpr, G = LPR / NB;
-    const int lane = t & (LPR - 1), c = lane % NB, g = lane / NB, rl = t >> llpr;
+    constexpr int CV = spmv_cv<NB>(), NG = NB / CV;
+    const int t = threadIdx.x, LPR = geo.lpr(), RPB = geo.rpb(), G = 1 << geo.lg;
+    const int lane = t & (LPR - 1), c0 = (lane % NG) * CV, g = lane / NG, rl = t >> geo.llpr;
     const int nblk = gridDim.x, b = xcd_block(blockIdx.x, nblk);
     const int span = ceil_div_dev(nrows, nblk * RPB) * RPB;
     const int r0 = b * span, r1 = min(nrows, r0 + span);
     EP epv = ep;
-    epv.prep(c);
+    epv.prep(c0);  // the epilogues of this kernel hold nothing per column
     constexpr int NVA = NV > 0 ? NV : 1;
-    double acc[NVA];
+    double acc[CV][NVA];
 #pragma unroll
-    for (int q = 0; q < NVA; ++q) acc[q] = 0.0;
+    for (int v = 0; v < CV; ++v)
+#pragma unroll
+        for (int q = 0; q < NVA; ++q) acc[v][q] = 0.0;
     constexpr int U = kSpmvUnroll;
     for (int base = r0; base < r1; base += RPB) {
         const int row = base + rl;
         const bool live = row < r1;
-        typename EP::P pr{};
-        if (live && g == 0) pr = epv.load(row, c);
-        T se = T(0), te = T(0);
+        typename EP::P pr[CV];
+        if (live && g == 0) {
+#pragma unroll
+            for (int v = 0; v < CV; ++v) pr[v] = epv.load(row, c0 + v);
+        }
+        T se[CV], te[CV];
+#pragma unroll
+        for (int v = 0; v < CV; ++v) se[v] = te[v] = T(0);
         if (live) {
             const int p1 = rp[row + 1];
             for (int p = rp[row] + g; p < p1; p += U * G) {
@@ -963,20 +990,28 @@ __global__ __launch_bounds__(kBlock) void tpro_kernel(int nrows, const int *__re
                     sa[u] = q < p1 ? s : T(0);
                 }
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const T ev = e[(size_t)kk[u] * NB + c];
-                    se += sa[u] * ev;
-                    te += ta[u] * ev;
-                }
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int v = 0; v < CV; ++v) {
+                        const T ev = e[(size_t)kk[u] * NB + c0 + v];
+                        se[v] += sa[u] * ev;
+                        te[v] += ta[u] * ev;
+                    }
             }
         }
-        for (int off = NB; off < LPR; off <<= 1) {  // the G groups of a row and column
-            se += __shfl_xor(se, off);
-            te += __shfl_xor(te, off);
+        for (int off = NG; off < LPR; off <<= 1) {  // the G groups of a row and column group
+#pragma unroll
+            for (int v = 0; v < CV; ++v) {
+                se[v] += __shfl_xor(se[v], off);
+                te[v] += __shfl_xor(te[v], off);
+            }
         }
-        if (live && g == 0) epv(row, c, se, te, pr, acc);
+        if (live && g == 0) {
+#pragma unroll
+            for (int v = 0; v < CV; ++v) epv(row, c0 + v, se[v], te[v], pr[v], acc[v]);
+        }
     }
-    if constexpr (NV > 0) block_partials<NV, NB>(acc, red);
+    if constexpr (NV > 0) block_partials_cv<NV, NB, CV>(acc, red);
 }
 
 // Chebyshev, first post step: y0 = t + S e (in place of t),

@@ -119,22 +119,16 @@ template <int NB> struct Solver {
         const DCsr &Tm = Lv.T;
         // the method's work here: the prolongation S e and the product A (x + S e)
         c.st.bytes += spmv_bytes(Lv.S.n, Lv.S.nnz, sizeof(T), NB) + spmv_bytes(Lv.A.n, Lv.A.nnz, sizeof(T), NB);
-        const double m = Tm.n > 0 ? (double)Tm.nnz / (double)Tm.n : 1.0;
-        int G = 1;
-        const int tl = Tm.tuned_lg[ilog2(NB)][std::is_same_v<T, float> ? 1 : 0];
-        if (tl >= 0) G = 1 << tl;  // the autotuner's choice
-        else
-            while (G * NB < 64 && G < m / kSpmvUnroll) G <<= 1;
-        const int llpr = ilog2(G * NB);
-        const int g = grid_rows(Tm.n, kBlock >> llpr, NV > 0 ? red_grid_max<NB>() : kMaxGridPlain);
+        const Geo geo = geo_for<NB, T>(Tm, true);
+        const int g = grid_rows(Tm.n, geo.rpb(), NV > 0 ? red_grid_max<NB>() : kMaxGridPlain);
         Reducer<(NV > 0 ? NV : 1), NB> red{part[pbuf]};
         if (NV > 0) pgrid[pbuf] = g;
         if (Lv.Tc16)
             hipLaunchKernelGGL((tpro_kernel<T, NB, NV, EP, uint16_t>), dim3(g), dim3(kBlock), 0, s, Tm.n, Tm.rp,
-                               Lv.Tc16, avals<T>(Tm), tsvals<T>(Lv), e, ep, llpr, red, stop);
+                               Lv.Tc16, avals<T>(Tm), tsvals<T>(Lv), e, ep, geo, red, stop);
         else
             hipLaunchKernelGGL((tpro_kernel<T, NB, NV, EP>), dim3(g), dim3(kBlock), 0, s, Tm.n, Tm.rp, Tm.ci,
-                               avals<T>(Tm), tsvals<T>(Lv), e, ep, llpr, red, stop);
+                               avals<T>(Tm), tsvals<T>(Lv), e, ep, geo, red, stop);
     }
 
     template <int NV, class OP, class FIN> void elem(int n, OP op, FIN fin, const int *stop, int pbuf = 0) {
