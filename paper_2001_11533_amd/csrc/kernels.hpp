@@ -1760,58 +1760,67 @@ __global__ __launch_bounds__(kBlock) void dense_apply1_kernel(int n, int ld, con
     }
 }
 
-template <typename T, typename TM, int NB>
-__global__ __launch_bounds__(kBlock) void dense_apply_kernel(int n, int ld, const TM *__restrict__ inv,
-                                                             const T *__restrict__ b, T *__restrict__ x,
-                                                             const int *__restrict__ stop) {
+// Several columns: x = Inv B on the FP64 matrix cores.  A workgroup forms 16
+// rows by all columns; its 16 wavefronts take the 16-entry chunks of the rows
+// in turn, each chunk four v_mfma_f64_16x16x4f64 (lane l: row l % 16, the
+// entries 4 (l / 16) .. + 3 of the chunk in one 16-byte load per four floats;
+// step e multiplies entry e of each lane, so the matrix operand's k and the
+// batch operand's k are permuted alike), four chunks' loads in flight, and
+// their sums are added through LDS in wavefront order.  The accumulation is
+// FP64 whatever T.  Columns past NB and rows past n are computed from clamped
+// reads and dropped; chunks past the last are zeroed (rows are zero-padded to
+// ld, so the ragged chunk needs only its batch index clamped).  Bound by the
+// matrix's and the batch's traffic into 100 CUs.  n = 1639, float32, 16 columns:
+// 9.7 us against 29.2 us of a wavefront per row on the vector ALUs, whose
+// lanes each read every column of the batch.
+constexpr int kMmWaves = 16;
+typedef double mm_v4d __attribute__((ext_vector_type(4)));
+template <typename T, int NB>
+__global__ __launch_bounds__(64 * kMmWaves) void dense_mm_kernel(int n, int ld, const T *__restrict__ inv,
+                                                                 const T *__restrict__ b, T *__restrict__ x,
+                                                                 const int *__restrict__ stop) {
     if (stop && *stop) return;
-    using V = Vec16<TM>;
+    using V = Vec16<T>;
     using VT = typename V::type;
-    constexpr int W = V::n, D = 4;
-    const int lane = threadIdx.x % 64;
-    const int w = (blockIdx.x * kBlock + threadIdx.x) / 64;
-    const int nw = gridDim.x * kBlock / 64;
-    for (int i = w; i < n; i += nw) {
-        double acc[NB];
+    constexpr int D = 4;
+    const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, kq = (l >> 4) * 4;
+    const int row0 = blockIdx.x * 16;
+    const T *row = inv + (size_t)min(row0 + (l & 15), n - 1) * ld;
+    const int col = min(l & 15, NB - 1);
+    const int nk = (n + 15) / 16;
+    mm_v4d acc = {0.0, 0.0, 0.0, 0.0};
+    for (int c0 = wv; c0 < nk; c0 += kMmWaves * D) {
+        VT m[D][4 / V::n];
+        T v[D][4];
 #pragma unroll
-        for (int c = 0; c < NB; ++c) acc[c] = 0.0;
-        const TM *row = inv + (size_t)i * ld;
-        for (int k0 = lane * W; k0 < n; k0 += 64 * W * D) {
-            // unconditional loads as in dense_apply1_kernel: entries past n
-            // read a valid entry again and are weighted by 0
-            VT m[D];
+        for (int u = 0; u < D; ++u) {
+            const int k = min(c0 + u * kMmWaves, nk - 1) * 16 + kq;
 #pragma unroll
-            for (int u = 0; u < D; ++u) {
-                const int k = k0 + u * 64 * W;
-                const VT mv = *reinterpret_cast<const VT *>(row + min(k, ld - W));
-                m[u] = k < n ? mv : VT{};
-            }
+            for (int q = 0; q < 4 / V::n; ++q) m[u][q] = *reinterpret_cast<const VT *>(row + k + q * V::n);
 #pragma unroll
-            for (int u = 0; u < D; ++u) {
-#pragma unroll
-                for (int e = 0; e < W; ++e) {
-                    const int k = k0 + u * 64 * W + e;
-                    const double a = k < n ? V::get(m[u], e) : 0.0;
-                    const size_t kc = (size_t)min(k, n - 1) * NB;
-#pragma unroll
-                    for (int c = 0; c < NB; ++c) acc[c] += a * (double)b[kc + c];
-                }
-            }
+            for (int e = 0; e < 4; ++e) v[u][e] = b[(size_t)min(k + e, n - 1) * NB + col];
         }
+        __builtin_amdgcn_sched_barrier(0);  // the loads stay together, ahead of their uses
 #pragma unroll
-        for (int c = 0; c < NB; ++c) {
-            double v = acc[c];
-            for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-            acc[c] = v;
-        }
-        if (lane < NB) {
-            double v = acc[0];
+        for (int u = 0; u < D; ++u) {
+            const bool on = c0 + u * kMmWaves < nk;
 #pragma unroll
-            for (int c = 1; c < NB; ++c)
-                if (lane == c) v = acc[c];
-            x[(size_t)i * NB + lane] = (T)v;
+            for (int e = 0; e < 4; ++e) {
+                const double a = on ? V::get(m[u][e / V::n], e % V::n) : 0.0;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)v[u][e], acc, 0, 0, 0);
+            }
         }
     }
+    __shared__ double red[kMmWaves][4][64];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[wv][r][l] = acc[r];
+    __syncthreads();
+    if (threadIdx.x >= 256) return;
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kMmWaves; ++w) s += red[w][wv][l];
+    const int i = row0 + (l >> 4) + 4 * wv;  // result r of lane l: row l / 16 + 4 r, column l % 16
+    if (i < n && (l & 15) < NB) x[(size_t)i * NB + (l & 15)] = (T)s;
 }
 
 }  // namespace amg

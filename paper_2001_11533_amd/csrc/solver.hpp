@@ -167,22 +167,17 @@ template <int NB> struct Solver {
     }
 
     template <typename T> void dense_apply(const DenseOp &d, const T *b, T *x, const int *stop) {
-        const int g = ceil_div((long)d.n * 64, kBlock);
         c.st.bytes += (double)sizeof(T) * ((double)d.n * d.n + 2.0 * d.n * NB);
+        const T *m;
+        if constexpr (std::is_same_v<T, float>) m = d.m32;
+        else m = d.m64;
         // the vector kernel reads b in 16-byte vectors: it needs one full vector
-        if (NB == 1 && reinterpret_cast<uintptr_t>(b) % 16 == 0 && d.n * sizeof(T) >= 16) {
-            const T *m;
-            if constexpr (std::is_same_v<T, float>) m = d.m32;
-            else m = d.m64;
-            hipLaunchKernelGGL((dense_apply1_kernel<T>), dim3(g), dim3(kBlock), 0, s, d.n, d.ld, m, b, x, stop);
-            return;
-        }
-        if constexpr (std::is_same_v<T, float>)
-            hipLaunchKernelGGL((dense_apply_kernel<T, float, NB>), dim3(g), dim3(kBlock), 0, s, d.n, d.ld, d.m32, b,
-                               x, stop);
+        if (NB == 1 && reinterpret_cast<uintptr_t>(b) % 16 == 0 && d.n * sizeof(T) >= 16)
+            hipLaunchKernelGGL((dense_apply1_kernel<T>), dim3(ceil_div((long)d.n * 64, kBlock)), dim3(kBlock), 0, s,
+                               d.n, d.ld, m, b, x, stop);
         else
-            hipLaunchKernelGGL((dense_apply_kernel<T, double, NB>), dim3(g), dim3(kBlock), 0, s, d.n, d.ld, d.m64,
-                               b, x, stop);
+            hipLaunchKernelGGL((dense_mm_kernel<T, NB>), dim3(ceil_div(d.n, 16)), dim3(64 * kMmWaves), 0, s, d.n,
+                               d.ld, m, b, x, stop);
     }
 
     void read_sc(const CgScal *d) {
