@@ -300,7 +300,7 @@ int amg_copy_dense(amg_ctx *ctx, int which, int32_t *n, double *out);
  * entries, batch width and value type, and apply it to the context.  Entries the table
  * already holds are applied without timing.  cache_path: NULL, or a JSON file read
  * first (if present) and rewritten with the whole table.  *n_timed (may be NULL): the
- * products timed by this call.  Products of the level-0 sliced-ELL copy (one column)
+ * products timed by this call.  Products of the level-0 sliced-ELL copy
  * have no such choice.  Results change only at rounding level (the order in which a
  * row's entries are summed).  Errors: ARG (reps < 1, an unreadable or malformed cache
  * file, or one that cannot be written), HIP. */
@@ -355,9 +355,10 @@ const char *amg_last_error(amg_ctx *ctx);
  * *ms_avg receives milliseconds per launch and *bytes the algorithmic bytes one
  * launch moves (row pointers, column indices and values once, every vector it
  * reads or gathers once, every vector it writes once; for which 4 the bytes of
- * the method's product q = A p: 4 (n+1) + (4 + 8) nnz(A_0) + 2 8 n nb).  Level-0 products with one
- * column run on a sliced-ELL copy whose columns are 16-bit offsets from a base
- * per slice of 64 rows (built when every slice spans fewer than 65536 columns),
+ * the method's product q = A p: 4 (n+1) + (4 + 8) nnz(A_0) + 2 8 n nb).  Level-0 products
+ * run on a sliced-ELL copy whose columns are 16-bit offsets from a base
+ * per slice of 64 rows (built when every slice spans fewer than 65536 columns; a
+ * batch uses it while its padding is at most half of the stored entries),
  * and T_0's columns are kept as 16-bit values when level 1 has at most 65536
  * nodes; such column indices count 2 bytes, all others 4.
  * Errors: ARG; NOCONV if a grid barrier wait of entry 5 timed out. */

@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kBlock) void step_kernel(int n, float *v) {
 // process-wide table keyed by device, matrix kind, size, stored entries, batch
 // width and value type; amg_autotune fills it (and reads / writes it as JSON),
 // amg_setup with opts.autotune = 1 applies what it holds.  The level-0 products
-// that run on the sliced-ELL copy (one column) have no such parameter.
+// that run on the sliced-ELL copy have no such parameter.
 struct TuneTable {
     std::mutex m;
     std::map<std::string, int> lg;
@@ -310,15 +310,15 @@ template <int NB, class F> void for_tunables(Ctx &c, F &&f) {
         if (prec == 32 && c.o.inner_precision != 32) continue;
         for (int l = 0; l < c.L; ++l) {
             Level &Lv = c.lev[l];
-            const bool sell = NB == 1 && Lv.A.sl_off;  // level 0: A and M run on the sliced-ELL copy
+            // products that run on the sliced-ELL copy (level 0) have no such choice
             const bool sell_vals = prec == 64 ? Lv.A.sl_v != nullptr : Lv.A.sl_v32 != nullptr;
-            if (!(sell && sell_vals)) f("A", Lv.A, l, prec, false);
+            if (!(Lv.A.sell_for(NB) && sell_vals)) f("A", Lv.A, l, prec, false);
             if (l + 1 < c.L) {
                 if (Lv.S.rp) f("S", Lv.S, l, prec, false);
                 if (Lv.St.rp) f("St", Lv.St, l, prec, false);
                 if (Lv.T.rp && (prec == 64 ? (Lv.T.v && Lv.Ts) : (Lv.T.v32 && Lv.Ts32))) f("T", Lv.T, l, prec, true);
             }
-            if (prec == 64 && !(sell && Lv.M.sl_v)) f("M", Lv.M, l, prec, false);
+            if (prec == 64 && !(Lv.M.sell_for(NB) && Lv.M.sl_v)) f("M", Lv.M, l, prec, false);
         }
     }
 }
@@ -1056,7 +1056,7 @@ int amg_time_kernel(amg_ctx *ctx, int which, int prec, int nb, int reps, double 
             // algorithmic bytes: row pointers, (col, val) per stored entry, x read
             // once, y written once (per column); a column takes 2 bytes in the
             // level-0 sliced-ELL copy (single column), else 4
-            auto ib = [&](int l) { return l == 0 && NB == 1 && c.lev[0].A.sl_off ? 2.0 : 4.0; };
+            auto ib = [&](int l) { return l == 0 && c.lev[0].A.sell_for(NB) ? 2.0 : 4.0; };
             const double spmv_b = 4.0 * (n + 1) + (ib(0) + sz) * L0.A.nnz + 2.0 * sz * n * nbd;
             hipEvent_t e0, e1;
             AMG_HIP(hipEventCreate(&e0));

@@ -188,12 +188,17 @@ struct DCsr {
     // copy exists only when every slice spans fewer than 65536 columns), and the
     // rows of a slice are padded to its longest with (offset 0, value 0)
     int nsl = 0;
+    long sl_tot = 0;        // stored entries, padding included
     bool sl_over8 = true;   // some slice is wider than 8 entries per row
     int *sl_off = nullptr;  // [nsl + 1]
     int *sl_base = nullptr; // [nsl]
     uint16_t *sl_cd = nullptr;
     double *sl_v = nullptr;
     float *sl_v32 = nullptr;
+    // whether products on nb columns run on the copy: always for one column; a
+    // batch, whose gathers and multiplications for a padded entry cost as much as
+    // for a stored one, only up to half as many again (3D P1 rows pad by 12 %)
+    bool sell_for(int nb) const { return sl_off && (nb == 1 || 2 * sl_tot <= 3L * nnz); }
     // lanes-per-row choice set by the autotuner: log2 G for batch width
     // 2^k (k = 0..4) and values FP64 (0) / float32 (1); -1 = the default rule
     int8_t tuned_lg[5][2] = {{-1, -1}, {-1, -1}, {-1, -1}, {-1, -1}, {-1, -1}};
@@ -204,7 +209,7 @@ constexpr int kMaxGrid = 16384;        // workgroups at most for kernels with re
 constexpr int kMaxGridPlain = 1 << 20; // and for kernels without
 // Reducing launches on NB columns: the partials of a finalize grow as grid x NB,
 // so wide batches take fewer (fuller) workgroups.
-template <int NB> constexpr int red_grid_max() { return NB <= 2 ? kMaxGrid : (2 * kMaxGrid) / NB; }
+template <int NB> constexpr int red_grid_max() { return NB <= 2 ? kMaxGrid : kMaxGrid / NB; }
 constexpr int kFinBlock = 1024;        // threads of a finalize kernel
 constexpr int kXcd = 8;          // XCDs of an MI355X
 

@@ -73,11 +73,22 @@ __device__ __forceinline__ void publish(CgScal *sc, int NBc) {
     m->all_conv = all;
 }
 
-__device__ __forceinline__ int xcd_block(int b, int nblk) {
-    // Workgroups are dispatched round-robin over the XCDs; give each XCD a
-    // contiguous run of row blocks so neighbouring rows share an L2.
-    const int per = nblk / kXcd;
-    return (b % kXcd) * per + b / kXcd;
+// A workgroup's share of nunits units of work (slices, row blocks, blocks of
+// elements): first, first + step, .. below end.  Workgroups are dispatched
+// round-robin over the XCDs, whose L2s are separate; each XCD gets a contiguous
+// run of units, so neighbouring rows share an L2, and when a launch has fewer
+// workgroups than units its workgroups sweep that run side by side: what one
+// gathers from its neighbours' rows is then at most a few steps old.  (A run of
+// units per workgroup, taken before, spread an XCD over 128 places at once and
+// fetched a gathered vector once per neighbour plane and line.)  rot shifts the
+// runs by rot XCDs.
+struct Share {
+    int first, end, step;
+};
+__device__ __forceinline__ Share xcd_share(int nunits, int rot = 0) {
+    const int per = gridDim.x / kXcd, x = (int)(blockIdx.x + rot) % kXcd;
+    const int run = ceil_div_dev(nunits, kXcd);
+    return {x * run + (int)(blockIdx.x / kXcd), min(nunits, (x + 1) * run), per};
 }
 
 // Columns per lane: a lane serves CV consecutive columns of the batch, so its
@@ -486,10 +497,7 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(int nrows, const int *__re
     const int t = threadIdx.x;
     const int LPR = geo.lpr(), RPB = geo.rpb(), G = 1 << geo.lg;
     const int lane = t & (LPR - 1), c0 = (lane % NG) * CV, g = lane / NG, rl = t >> geo.llpr;
-    const int nblk = gridDim.x, b = xcd_block(blockIdx.x, nblk);
-    const int span = ceil_div_dev(nrows, nblk * RPB) * RPB;
-    const int r0 = b * span;
-    const int r1 = min(nrows, r0 + span);
+    const Share sh = xcd_share(ceil_div_dev(nrows, RPB));
     GX gxv[CV];
     EP epv[CV];
 #pragma unroll
@@ -515,9 +523,9 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(int nrows, const int *__re
 #pragma unroll
         for (int q = 0; q < NVA; ++q) acc[v][q] = 0.0;
     constexpr int U = kSpmvUnroll;  // entries per lane issued together
-    for (int base = r0; base < r1; base += RPB) {
-        const int row = base + rl;
-        const bool live = row < r1;
+    for (int blk = sh.first; blk < sh.end; blk += sh.step) {
+        const int row = blk * RPB + rl;
+        const bool live = row < nrows;
         typename EP::P pr[CV];
         if (live && g == 0) {
 #pragma unroll
@@ -560,43 +568,63 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(int nrows, const int *__re
     if constexpr (NV > 0) block_partials_cv<NV, NB, CV>(acc, red);
 }
 
-// The same product over the sliced-ELL copy (single column): one wavefront
-// per slice of 64 rows, one lane per row; a lane issues the loads of up to U
-// entries of its row at once, with no dependence on row pointers (U = 8 when
-// no slice is wider, as for 5- and 7-point rows, else 16).  Columns are
+// The same product over the sliced-ELL copy: NG lanes per row, CV columns each
+// (one column: a wavefront per slice of 64 rows, a lane per row; 16 columns: a
+// workgroup per slice).  A lane issues the loads of up to U entries of its row
+// at once, with no dependence on row pointers, then their gathers.  U is 8 when
+// no slice is wider (5- and 7-point rows) and for a batch, whose gathers are CV
+// values each; one column takes wider rows in one round of 16.  Columns are
 // 16-bit offsets from the slice's base column (6 bytes per float32 entry).
 // xrot rotates the XCD-contiguous block ranges by xrot XCDs (0 in solves).
-template <typename T, int NV, class GX, class EP, class PRO = NoPro, int U = 16>
+template <int NB> constexpr int sell_slices() { return kBlock / (NB / spmv_cv<NB>()) / 64; }  // per workgroup
+
+template <typename T, int NB, int NV, class GX, class EP, class PRO = NoPro, int U = 16>
 __global__ __launch_bounds__(kBlock) void sell_kernel(int nrows, int nsl, const int *__restrict__ soff,
                                                       const int *__restrict__ sbase,
                                                       const uint16_t *__restrict__ cd, const T *__restrict__ av, GX gx,
-                                                      EP ep, Reducer<(NV > 0 ? NV : 1), 1> red,
+                                                      EP ep, Reducer<(NV > 0 ? NV : 1), NB> red,
                                                       const int *__restrict__ stop, PRO pro = PRO{}, int xrot = 0) {
     if (stop && *stop) return;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int nblk = gridDim.x, b = (xcd_block(blockIdx.x, nblk) + xrot * (nblk / kXcd)) % nblk;
-    constexpr int WPB = kBlock / 64;
-    const int per = ceil_div_dev(nsl, nblk * WPB) * WPB;  // contiguous slices per workgroup
-    const int s0 = b * per, s1 = min(nsl, s0 + per);
-    gx.prep(0);
-    ep.prep(0);
+    constexpr int CV = spmv_cv<NB>(), NG = NB / CV, SPB = sell_slices<NB>();
+    const int c0 = (threadIdx.x % NG) * CV, rl = threadIdx.x / NG, lane = rl & 63;
+    const Share sh = xcd_share(ceil_div_dev(nsl, SPB), xrot);
+    GX gxv[CV];
+    EP epv[CV];
+#pragma unroll
+    for (int v = 0; v < CV; ++v) {
+        gxv[v] = gx;
+        gxv[v].prep(c0 + v);
+        epv[v] = ep;
+        epv[v].prep(c0 + v);
+    }
     if constexpr (PRO::active) {  // the previous iteration's finalize, then this one
         const double *fb;
         if (fused_fin(pro, fb)) return;
-        gx.set_beta(fb[0]);
-        ep.set_beta(fb[0]);
+#pragma unroll
+        for (int v = 0; v < CV; ++v) {
+            gxv[v].set_beta(fb[c0 + v]);
+            epv[v].set_beta(fb[c0 + v]);
+        }
     }
     constexpr int NVA = NV > 0 ? NV : 1;
-    double acc[NVA];
+    double acc[CV][NVA];
 #pragma unroll
-    for (int v = 0; v < NVA; ++v) acc[v] = 0.0;
-    for (int sl = s0 + wv; sl < s1; sl += WPB) {
+    for (int v = 0; v < CV; ++v)
+#pragma unroll
+        for (int q = 0; q < NVA; ++q) acc[v][q] = 0.0;
+    for (int blk = sh.first; blk < sh.end; blk += sh.step) {
+        const int sl = blk * SPB + __builtin_amdgcn_readfirstlane(rl >> 6);  // one slice per wavefront
+        if (SPB > 1 && sl >= nsl) break;
         const int row = sl * 64 + lane;
         const bool live = row < nrows;
-        typename EP::P pr{};
-        if (live) pr = ep.load(row, 0);
+        typename EP::P pr[CV] = {};
+        if (live)
+#pragma unroll
+            for (int v = 0; v < CV; ++v) pr[v] = epv[v].load(row, c0 + v);
         const int o = soff[sl], w = (soff[sl + 1] - o) >> 6, cb = sbase[sl];
-        T sum = T(0);
+        T sum[CV];
+#pragma unroll
+        for (int v = 0; v < CV; ++v) sum[v] = T(0);
         for (int k0 = 0; k0 < w; k0 += U) {
             // Every load is unconditional (entries past the slice's width read
             // its last entry again, weighted by 0), so the U column and value
@@ -613,11 +641,15 @@ __global__ __launch_bounds__(kBlock) void sell_kernel(int nrows, int nsl, const 
                 aa[u] = k0 + u < w ? a : T(0);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) sum += aa[u] * gx(kk[u], 0);
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int v = 0; v < CV; ++v) sum[v] += aa[u] * gxv[v](kk[u], c0 + v);
         }
-        if (live) ep(row, 0, sum, pr, acc);
+        if (live)
+#pragma unroll
+            for (int v = 0; v < CV; ++v) epv[v](row, c0 + v, sum[v], pr[v], acc[v]);
     }
-    if constexpr (NV > 0) block_partials<NV, 1>(acc, red);
+    if constexpr (NV > 0) block_partials_cv<NV, NB, CV>(acc, red);
 }
 
 // Elementwise kernel over n rows x NB columns with fused reductions.
@@ -626,17 +658,17 @@ __global__ __launch_bounds__(kBlock) void elem_kernel(int n, OP op, Reducer<(NV 
                                                       const int *__restrict__ stop) {
     if (stop && *stop) return;
     const int t = threadIdx.x, c = t % NB;
-    const int nblk = gridDim.x, b = xcd_block(blockIdx.x, nblk);
     const long total = (long)n * NB;
-    const long span = (long)ceil_div_dev_l(total, (long)nblk * kBlock) * kBlock;
-    const long e0 = (long)b * span;
-    const long e1 = total < e0 + span ? total : e0 + span;
+    const Share sh = xcd_share((int)ceil_div_dev_l(total, kBlock));
     op.prep(c);
     constexpr int NVA = NV > 0 ? NV : 1;
     double acc[NVA];
 #pragma unroll
     for (int v = 0; v < NVA; ++v) acc[v] = 0.0;
-    for (long e = e0 + t; e < e1; e += kBlock) op((int)(e / NB), c, acc);
+    for (int blk = sh.first; blk < sh.end; blk += sh.step) {
+        const long e = (long)blk * kBlock + t;
+        if (e < total) op((int)(e / NB), c, acc);
+    }
     if constexpr (NV > 0) block_partials<NV, NB>(acc, red);
 }
 
@@ -705,15 +737,14 @@ __global__ __launch_bounds__(kBlock) void cg_update_kernel(int n, T *__restrict_
     const int c = t % NB;
     const T a = (T)sh_a[c];
     const int live = sh_live[c];
-    const int nblk = gridDim.x, b = xcd_block(blockIdx.x, nblk);
     const long total = (long)n * NB;
-    const long span = (long)ceil_div_dev_l(total, (long)nblk * kBlock) * kBlock;
-    const long e0 = (long)b * span;
-    const long e1 = total < e0 + span ? total : e0 + span;
+    const Share sh = xcd_share((int)ceil_div_dev_l(total, kBlock));
     double acc[JAC ? 2 : 1] = {};
     if (live) {
-        for (long e = e0 + t; e < e1; e += kBlock) {
-            const size_t o = (size_t)e;
+        for (int blk = sh.first; blk < sh.end; blk += sh.step) {
+            const size_t o = (size_t)blk * kBlock + t;
+            if ((long)o >= total) break;
+            const size_t e = o;
             x[o] += a * p[o];
             const T rv = r[o] - a * q[o];
             r[o] = rv;
@@ -951,9 +982,7 @@ __global__ __launch_bounds__(kBlock) void tpro_kernel(int nrows, const int *__re
     constexpr int CV = spmv_cv<NB>(), NG = NB / CV;
     const int t = threadIdx.x, LPR = geo.lpr(), RPB = geo.rpb(), G = 1 << geo.lg;
     const int lane = t & (LPR - 1), c0 = (lane % NG) * CV, g = lane / NG, rl = t >> geo.llpr;
-    const int nblk = gridDim.x, b = xcd_block(blockIdx.x, nblk);
-    const int span = ceil_div_dev(nrows, nblk * RPB) * RPB;
-    const int r0 = b * span, r1 = min(nrows, r0 + span);
+    const Share sh = xcd_share(ceil_div_dev(nrows, RPB));
     EP epv = ep;
     epv.prep(c0);  // the epilogues of this kernel hold nothing per column
     constexpr int NVA = NV > 0 ? NV : 1;
@@ -963,9 +992,9 @@ __global__ __launch_bounds__(kBlock) void tpro_kernel(int nrows, const int *__re
 #pragma unroll
         for (int q = 0; q < NVA; ++q) acc[v][q] = 0.0;
     constexpr int U = kSpmvUnroll;
-    for (int base = r0; base < r1; base += RPB) {
-        const int row = base + rl;
-        const bool live = row < r1;
+    for (int blk = sh.first; blk < sh.end; blk += sh.step) {
+        const int row = blk * RPB + rl;
+        const bool live = row < nrows;
         typename EP::P pr[CV];
         if (live && g == 0) {
 #pragma unroll

@@ -2364,6 +2364,7 @@ struct Setup {
             hipLaunchKernelGGL(k_to_f32, dim3(gsz(tot)), dim3(kBlock), 0, s, (long)tot, A.sl_v, A.sl_v32);
         }
         A.nsl = nsl;
+        A.sl_tot = tot;
         check_kernels();
     }
 

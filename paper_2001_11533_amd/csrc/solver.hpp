@@ -74,7 +74,7 @@ template <int NB> struct Solver {
 
     // workgroups of a reducing product with A (the partials it leaves)
     template <typename T> int red_grid(const DCsr &A) const {
-        if (NB == 1 && A.sl_off) return grid_rows(A.nsl, kBlock / 64, red_grid_max<NB>());
+        if (A.sell_for(NB)) return grid_rows(A.nsl, sell_slices<NB>(), red_grid_max<NB>());
         return grid_rows(A.n, geo_for<NB, T>(A).rpb(), red_grid_max<NB>());
     }
 
@@ -82,23 +82,21 @@ template <int NB> struct Solver {
     void spmv(const DCsr &A, const T *vals, GX gx, EP ep, FIN fin, const int *stop, int pbuf = 0,
               PRO pro = PRO{}) {
         c.st.bytes += spmv_bytes(A.n, A.nnz, sizeof(T), NB);
-        if constexpr (NB == 1) {
-            const T *sv = nullptr;
-            if constexpr (std::is_same_v<T, float>) sv = vals == A.v32 ? A.sl_v32 : nullptr;
-            else sv = vals == A.v ? A.sl_v : nullptr;
-            if (A.sl_off && sv) {
-                const int g = grid_rows(A.nsl, kBlock / 64, NV > 0 ? red_grid_max<NB>() : kMaxGridPlain);
-                Reducer<(NV > 0 ? NV : 1), NB> red{part[pbuf]};
-                if (NV > 0) pgrid[pbuf] = g;
-                if (!A.sl_over8)
-                    hipLaunchKernelGGL((sell_kernel<T, NV, GX, EP, PRO, 8>), dim3(g), dim3(kBlock), 0, s, A.n,
-                                       A.nsl, A.sl_off, A.sl_base, A.sl_cd, sv, gx, ep, red, stop, pro, xrot);
-                else
-                    hipLaunchKernelGGL((sell_kernel<T, NV, GX, EP, PRO, 16>), dim3(g), dim3(kBlock), 0, s, A.n,
-                                       A.nsl, A.sl_off, A.sl_base, A.sl_cd, sv, gx, ep, red, stop, pro, xrot);
-                finish<NV>(pbuf, fin, stop);
-                return;
-            }
+        const T *sv = nullptr;
+        if constexpr (std::is_same_v<T, float>) sv = vals == A.v32 ? A.sl_v32 : nullptr;
+        else sv = vals == A.v ? A.sl_v : nullptr;
+        if (A.sell_for(NB) && sv) {
+            const int g = grid_rows(A.nsl, sell_slices<NB>(), NV > 0 ? red_grid_max<NB>() : kMaxGridPlain);
+            Reducer<(NV > 0 ? NV : 1), NB> red{part[pbuf]};
+            if (NV > 0) pgrid[pbuf] = g;
+            if (NB > 1 || !A.sl_over8)
+                hipLaunchKernelGGL((sell_kernel<T, NB, NV, GX, EP, PRO, 8>), dim3(g), dim3(kBlock), 0, s, A.n, A.nsl,
+                                   A.sl_off, A.sl_base, A.sl_cd, sv, gx, ep, red, stop, pro, xrot);
+            else
+                hipLaunchKernelGGL((sell_kernel<T, NB, NV, GX, EP, PRO, NB == 1 ? 16 : 8>), dim3(g), dim3(kBlock), 0,
+                                   s, A.n, A.nsl, A.sl_off, A.sl_base, A.sl_cd, sv, gx, ep, red, stop, pro, xrot);
+            finish<NV>(pbuf, fin, stop);
+            return;
         }
         const Geo geo = geo_for<NB, T>(A);
         const int g = grid_rows(A.n, geo.rpb(), NV > 0 ? red_grid_max<NB>() : kMaxGridPlain);
