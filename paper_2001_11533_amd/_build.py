@@ -17,6 +17,9 @@ ARCH = "gfx950"
 # Packed FP32 instructions are disabled for device code (the host pass warns
 # that it does not know the feature; that is harmless).
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# The first sixteen words of a kernel's arguments arrive in registers with the
+# wavefront, without a load.
+DEVICE_FLAGS += ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", f"-I{INC}", "-Wno-unused-command-line-argument"]
 
 SOURCES = [("setup.hip", "hip"), ("api.hip", "hip"), ("assemble_gpu.hip", "hip"), ("assemble.cpp", "hip")]

@@ -554,6 +554,8 @@ int amg_setup(const amg_csr *A, const amg_csr *M, const uint8_t *dirichlet, cons
         c.dscratch = c.arena.alloc<double>(64);
         c.iscratch = c.arena.alloc<int>(64);
         c.iscratch2 = c.arena.alloc<int>(64);
+        c.never = c.arena.alloc<int>(1);
+        AMG_HIP(hipMemsetAsync(c.never, 0, sizeof(int), c.stream));
         AMG_HIP(hipHostMalloc((void **)&c.hsc, sizeof(CgScal), hipHostMallocDefault));
         AMG_HIP(hipHostMalloc((void **)&c.hscr, 64 * sizeof(double), hipHostMallocDefault));
         AMG_HIP(hipHostMalloc((void **)&c.hiscr, 64 * sizeof(int), hipHostMallocDefault));

@@ -158,6 +158,7 @@ struct Ctx {
     int pgrid[3] = {0, 0, 0};                       // workgroups that wrote each buffer
     double *dscratch = nullptr;  // small device scalars [64]
     int *iscratch = nullptr;     // small device ints [64]
+    int *never = nullptr;        // a stop flag that stays zero (kernels launched without one)
     // host mirrors
     CgScal *hsc = nullptr;       // pinned
     double *hscr = nullptr;      // pinned [64]

@@ -73,22 +73,89 @@ __device__ __forceinline__ void publish(CgScal *sc, int NBc) {
     m->all_conv = all;
 }
 
-// A workgroup's share of nunits units of work (slices, row blocks, blocks of
+// A workgroup's share of n units of work (slices, row blocks, blocks of
 // elements): first, first + step, .. below end.  Workgroups are dispatched
 // round-robin over the XCDs, whose L2s are separate; each XCD gets a contiguous
 // run of units, so neighbouring rows share an L2, and when a launch has fewer
 // workgroups than units its workgroups sweep that run side by side: what one
 // gathers from its neighbours' rows is then at most a few steps old.  (A run of
 // units per workgroup, taken before, spread an XCD over 128 places at once and
-// fetched a gathered vector once per neighbour plane and line.)  rot shifts the
-// runs by rot XCDs.
+// fetched a gathered vector once per neighbour plane and line.)  The counts
+// come from the host: dividing by the rows of a block took the kernel's first
+// hundred cycles.  rot shifts the runs by rot XCDs.
+struct Units {
+    int n, run, step;  // units, units per XCD, workgroups per XCD
+};
+inline Units units(int n, int grid) { return {n, ceil_div(n, kXcd), grid / kXcd}; }
 struct Share {
     int first, end, step;
 };
-__device__ __forceinline__ Share xcd_share(int nunits, int rot = 0) {
-    const int per = gridDim.x / kXcd, x = (int)(blockIdx.x + rot) % kXcd;
-    const int run = ceil_div_dev(nunits, kXcd);
-    return {x * run + (int)(blockIdx.x / kXcd), min(nunits, (x + 1) * run), per};
+__device__ __forceinline__ Share xcd_share(int n, int run, int step, int rot = 0) {
+    const int x = (int)((blockIdx.x + (unsigned)rot) % kXcd);
+    return {x * run + (int)(blockIdx.x / kXcd), min(n, (x + 1) * run), step};
+}
+
+// Small launches spend their time in a chain of waits (about 0.6 us each on a
+// first touch): kernel arguments, stop flag, row pointers, entries, gathers.
+// Scalar arguments therefore come first in every solve kernel, where the
+// hardware preloads them into registers, and these helpers keep loads that
+// need nothing but the arguments ahead of the test of the stop flag, so that
+// the waits overlap: the compiler would otherwise move them behind the branch.
+// pin: the loads of these values are issued, and waited for, here.
+__device__ __forceinline__ void pin_s(int a, int b = 0, int c = 0, int d = 0) { asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d)); }
+template <class V> __device__ __forceinline__ void pin_v(V a, V b) { asm volatile("" ::"v"(a), "v"(b)); }
+// the same for a functor's pointers and scalars
+template <class F> __device__ __forceinline__ void pin_args(const F &f) {
+    if constexpr (sizeof(F) % 8 == 0) {
+        const unsigned long long *w = reinterpret_cast<const unsigned long long *>(&f);
+#pragma unroll
+        for (size_t i = 0; i < sizeof(F) / 8; ++i) asm volatile("" ::"s"(w[i]));
+    }
+}
+
+// ---------------------------------------------------------------------------
+// x plus its value OFF lanes away (lane index xor OFF), for OFF = NG, 2 NG, ..
+// in ascending order: the sum over the lanes of a wavefront that agree modulo
+// NG, left in all of them.  Within 16 lanes by DPP, across them by gfx950's
+// row swaps; a shuffle through LDS per step costs about a hundred cycles.
+// The mirrors stand in for xor 4 (NG = 1 only) once the lanes of a quad agree.
+template <int CTRL> __device__ __forceinline__ int dpp_i(int x) {
+    return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false);
+}
+template <int OFF, int NG> __device__ __forceinline__ void lane_pair(int x, int &a, int &b) {
+    a = x;
+    if constexpr (OFF == 1) b = dpp_i<0xB1>(x);                      // quad_perm 1 0 3 2
+    else if constexpr (OFF == 2) b = dpp_i<0x4E>(x);                 // quad_perm 2 3 0 1
+    else if constexpr (OFF == 4 && NG == 1) b = dpp_i<0x141>(x);     // row_half_mirror
+    else if constexpr (OFF == 4) b = __builtin_amdgcn_ds_swizzle(x, (4 << 10) | 0x1f);
+    else if constexpr (OFF == 8) b = dpp_i<0x128>(x);                // row_ror 8
+    else if constexpr (OFF == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        a = (int)r[0];
+        b = (int)r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        a = (int)r[0];
+        b = (int)r[1];
+    }
+}
+template <int OFF, int NG> __device__ __forceinline__ float lane_add(float x) {
+    int a, b;
+    lane_pair<OFF, NG>(__float_as_int(x), a, b);
+    return __int_as_float(a) + __int_as_float(b);
+}
+template <int OFF, int NG> __device__ __forceinline__ double lane_add(double x) {
+    int al, bl, ah, bh;
+    lane_pair<OFF, NG>(__double2loint(x), al, bl);
+    lane_pair<OFF, NG>(__double2hiint(x), ah, bh);
+    return __hiloint2double(ah, al) + __hiloint2double(bh, bl);
+}
+// over the lanes of groups of LIM (a power of two, the same for the wavefront)
+template <int NG, typename T, int OFF = NG> __device__ __forceinline__ T group_add(T x, int lim) {
+    if constexpr (OFF < 64) {
+        if (OFF < lim) x = group_add<NG, T, 2 * OFF>(lane_add<OFF, NG>(x), lim);
+    }
+    return x;
 }
 
 // Columns per lane: a lane serves CV consecutive columns of the batch, so its
@@ -104,7 +171,7 @@ struct Geo {
     __host__ __device__ int rpb() const { return kBlock >> llpr; }
 };
 
-inline int ilog2(int x) {
+__host__ __device__ constexpr int ilog2(int x) {
     int l = 0;
     while ((1 << (l + 1)) <= x) ++l;
     return l;
@@ -144,7 +211,7 @@ template <int NB> inline Geo make_geo(long nnz, long rows, bool t32 = false) {
 }
 
 // the geometry with G = 2^lg lanes per (row, column group)
-template <int NB> inline Geo geo_from_lg(int lg) {
+template <int NB> __host__ __device__ inline Geo geo_from_lg(int lg) {
     Geo geo;
     geo.lg = lg;
     geo.llpr = lg + ilog2(NB / spmv_cv<NB>());
@@ -189,9 +256,7 @@ __device__ void block_partials_cv(const double (&acc)[CV][NV], Reducer<NV, NB> r
     for (int v = 0; v < CV; ++v)
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
-            double x = acc[v][q];
-#pragma unroll
-            for (int off = NG; off < 64; off <<= 1) x += __shfl_xor(x, off);
+            const double x = group_add<NG>(acc[v][q], 64);
             if (lane < NG) wred[t >> 6][q][lane * CV + v] = x;
         }
     __syncthreads();
@@ -217,8 +282,12 @@ __device__ void block_partials(const double (&acc)[NV], Reducer<NV, NB> r) {
 // wavefronts through LDS.  The order depends only on the counts, so every
 // workgroup that sums the same partials gets the same totals.  out (LDS,
 // [Q]) holds the totals for every thread on return.
-template <int Q, int BS, class SRC>
-__device__ void sum_quantities(SRC src, double *out) {
+// between() runs behind the first round of loads.
+struct NoBetween {
+    __device__ void operator()() const {}
+};
+template <int Q, int BS, class SRC, class BTW = NoBetween>
+__device__ void sum_quantities(SRC src, double *out, BTW between = BTW{}) {
     constexpr int LPS = pow2floor(BS / Q);
     constexpr int W = LPS < 64 ? LPS : 64;
     __shared__ double wsum[BS / 64];
@@ -229,8 +298,19 @@ __device__ void sum_quantities(SRC src, double *out) {
         const double *pp;
         int nblk;
         src(q, pp, nblk);
-        double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        int b = sub;
+        // the first round: up to eight per lane, unconditional loads (clamped
+        // index) added only where valid, so all are in flight together
+        double a[8];
+        {
+            const int last = nblk > 0 ? nblk - 1 : 0;
+            double v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = pp[min(sub + k * LPS, last)];
+            between();
+#pragma unroll
+            for (int k = 0; k < 8; ++k) a[k] = sub + k * LPS < nblk ? v[k] : 0.0;
+        }
+        int b = sub + 8 * LPS;
         for (; b + 7 * LPS < nblk; b += 8 * LPS) {
             double v[8];
 #pragma unroll
@@ -238,18 +318,19 @@ __device__ void sum_quantities(SRC src, double *out) {
 #pragma unroll
             for (int k = 0; k < 8; ++k) a[k] += v[k];
         }
-        // at most seven left: loaded unconditionally (clamped index), added
-        // only where valid, so the seven loads are in flight together
-        const int last = nblk > 0 ? nblk - 1 : 0;
-        double v[7];
+        // at most seven left
+        if (b < nblk) {
+            double v[7];
 #pragma unroll
-        for (int k = 0; k < 7; ++k) v[k] = pp[min(b + k * LPS, last)];
+            for (int k = 0; k < 7; ++k) v[k] = pp[min(b + k * LPS, nblk - 1)];
 #pragma unroll
-        for (int k = 0; k < 7; ++k) a[k] = b + k * LPS < nblk ? a[k] + v[k] : a[k];
+            for (int k = 0; k < 7; ++k) a[k] = b + k * LPS < nblk ? a[k] + v[k] : a[k];
+        }
         s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+    } else {
+        between();
     }
-#pragma unroll
-    for (int off = W / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+    s = group_add<1>(s, W);
     if constexpr (LPS > 64) {
         if ((t & 63) == 0) wsum[t >> 6] = s;
         __syncthreads();
@@ -266,14 +347,14 @@ __device__ void sum_quantities(SRC src, double *out) {
 }
 
 // The partials of NV quantities x NB columns, quantity-major ([NV*NB][nblk]).
-template <int NV, int NB, int BS = kBlock>
-__device__ void sum_partials(const double *__restrict__ partial, int nblk, double (&tot)[NV][NB]) {
+template <int NV, int NB, int BS = kBlock, class BTW = NoBetween>
+__device__ void sum_partials(const double *__restrict__ partial, int nblk, double (&tot)[NV][NB], BTW between = BTW{}) {
     sum_quantities<NV * NB, BS>(
         [&](int q, const double *&pp, int &n) {
             pp = partial + (size_t)q * nblk;
             n = nblk;
         },
-        &tot[0][0]);
+        &tot[0][0], between);
 }
 
 // Two buffers of one quantity x NB columns each, summed together.
@@ -343,77 +424,70 @@ template <int NB, bool JAC>
 __device__ bool fused_fin(const FusedFin<NB, JAC> &f, const double *&beta) {
     __shared__ double t1[JAC ? 2 : 1][NB], t2[1][NB];
     __shared__ double sb[NB];
-    __shared__ int sall;
-    // the column scalars the step reads, loaded before the partial sums so that
-    // both loads are in flight together (nothing written in this kernel
-    // changes what the step decides from them: see above)
-    ColScal pre[NB];  // conv, bad, tol2 and rho only
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int c = 0; c < NB; ++c) {
-            pre[c].conv = f.sc->s[c].conv;
-            pre[c].bad = f.sc->s[c].bad;
-            pre[c].tol2 = f.sc->s[c].tol2;
-            pre[c].rho = f.sc->s[c].rho;
-        }
+    __shared__ int sconv[NB];
+    const int t = threadIdx.x;
+    // the column scalars the step reads, thread c column c, loaded before the
+    // partial sums so that both loads are in flight together (nothing written in
+    // this kernel changes what the step decides from them: see above)
+    ColScal pre;  // conv, bad, tol2 and rho only
+    if (t < NB) {
+        pre.conv = f.sc->s[t].conv;
+        pre.bad = f.sc->s[t].bad;
+        pre.tol2 = f.sc->s[t].tol2;
+        pre.rho = f.sc->s[t].rho;
+    }
     if constexpr (JAC) sum_partials<2, NB>(f.p1, f.n1, t1);
     else sum_partials2<NB>(f.p1, f.n1, f.p2, f.n2, t1, t2);
-    if (threadIdx.x == 0) {
-        int all = 1;
-#pragma unroll
-        for (int c = 0; c < NB; ++c) {
-            ColScal &s = f.sc->s[c];
-            const double rr = t1[0][c], rz = JAC ? t1[1][c] : t2[0][c];
-            const int was = pre[c].conv;
-            int conv, bad;
-            const double b = cg_col_step(pre[c], rr, rz, conv, bad);
-            if (blockIdx.x == 0 && !was) {
-                s.iters += 1;
-                s.rr = rr;
-                s.rz = rz;
-                s.beta = b;
-                s.rho_next = rz;
-                s.bad = bad;
-                s.conv = conv;
-            }
-            sb[c] = b;
-            all &= conv;
+    if (t < NB) {
+        ColScal &s = f.sc->s[t];
+        const double rr = t1[0][t], rz = JAC ? t1[1][t] : t2[0][t];
+        int conv, bad;
+        const double b = cg_col_step(pre, rr, rz, conv, bad);
+        if (blockIdx.x == 0 && !pre.conv) {
+            s.iters += 1;
+            s.rr = rr;
+            s.rz = rz;
+            s.beta = b;
+            s.rho_next = rz;
+            s.bad = bad;
+            s.conv = conv;
         }
-        sall = all;
-        if (blockIdx.x == 0) publish(f.sc, NB);
+        sb[t] = b;
+        sconv[t] = conv;
     }
     __syncthreads();
+    if (blockIdx.x == 0 && t == 0) publish(f.sc, NB);
+    int all = 1;
+#pragma unroll
+    for (int c = 0; c < NB; ++c) all &= sconv[c];
     beta = sb;
-    return sall != 0;
+    return all != 0;
 }
 
 // The same step as a finalize kernel (after the last update a CG is allowed).
 template <int NB, bool JAC> struct FinFusedTail {
     CgScal *sc;
-    __device__ void step(const double (&rr)[NB], const double (&rz)[NB]) const {
-        for (int c = 0; c < NB; ++c) {
-            ColScal &s = sc->s[c];
-            if (s.conv) continue;
-            int conv, bad;
-            const double b = cg_col_step(s, rr[c], rz[c], conv, bad);
-            s.iters += 1;
-            s.rr = rr[c];
-            s.rz = rz[c];
-            s.beta = b;
-            s.rho_next = rz[c];
-            s.bad = bad;
-            s.conv = conv;
-        }
-        publish(sc, NB);
+    __device__ void head() const {}
+    __device__ void col(int c, double rr, double rz) const {
+        ColScal &s = sc->s[c];
+        if (s.conv) return;
+        int conv, bad;
+        const double b = cg_col_step(s, rr, rz, conv, bad);
+        s.iters += 1;
+        s.rr = rr;
+        s.rz = rz;
+        s.beta = b;
+        s.rho_next = rz;
+        s.bad = bad;
+        s.conv = conv;
     }
-    __device__ void operator()(double (&tot)[2][NB]) const { step(tot[0], tot[1]); }  // Jacobi
-    __device__ void operator()(double (&rr)[1][NB], double (&rz)[1][NB]) const { step(rr[0], rz[0]); }
 };
 
-// Finalize functors that keep their CG's scalars in a member sc (CgScal *)
-// run on a copy of them in LDS: the workgroup loads the block at once and
-// writes it back after the step, so thread 0's loop over the columns makes
-// no chain of dependent global loads (one per column and field before).
+// Finalize functors that keep their CG's scalars in a member sc (CgScal *) have
+// a step per column, col(c, totals of column c ..), and a head() for what
+// belongs to the CG.  They run on a copy of the scalars in LDS, loaded at once
+// and written back after the step, column c on thread c (thread 0 looping over
+// the columns: 7.8 us per finalize of 16 columns and one quantity, 4.9 us so).
 template <class F, class = void> struct fin_has_sc : std::false_type {};
 template <class F>
 struct fin_has_sc<F, std::void_t<decltype(std::declval<F &>().sc)>>
@@ -429,34 +503,41 @@ __device__ __forceinline__ unsigned long long sc_stage_load(const CgScal *sc) {
 
 // the step on the LDS copy (loaded by sc_stage_load before the partial sums,
 // so both loads are in flight together), then the copy back
-template <class FIN, class STEP>
+template <int NB, class FIN, class STEP>
 __device__ __forceinline__ void fin_staged(const FIN &fin, unsigned long long w, STEP step) {
     __shared__ CgScal lsc;
     const int t = threadIdx.x;
     if (t < kScWords) reinterpret_cast<unsigned long long *>(&lsc)[t] = w;
     __syncthreads();
-    if (t == 0) {
+    if (t < NB) {
         FIN f = fin;
         f.sc = &lsc;
-        step(f);
+        if (t == 0) f.head();
+        step(f, t);
     }
+    __syncthreads();
+    if (t == 0) publish(&lsc, NB);
     __syncthreads();
     if (t < kScWords) reinterpret_cast<unsigned long long *>(fin.sc)[t] = reinterpret_cast<unsigned long long *>(&lsc)[t];
 }
 
-// One workgroup: totals of the partials, then the finalize step on thread 0.
+// One workgroup: totals of the partials, then the finalize step.
 template <int NV, int NB, class FIN>
 __global__ __launch_bounds__(kFinBlock) void fin_kernel(const double *__restrict__ partial, int nblk, FIN fin,
                                                         const int *__restrict__ stop) {
-    if (stop && *stop) return;
     __shared__ double tot[NV][NB];
+    const int st = stop ? *stop : 0;  // tested after the sums, whose loads it does not hold up
     if constexpr (fin_has_sc<FIN>::value) {
         const unsigned long long w = sc_stage_load(fin.sc);
         sum_partials<NV, NB, kFinBlock>(partial, nblk, tot);
-        fin_staged(fin, w, [&](const FIN &f) { f(tot); });
+        if (st) return;
+        fin_staged<NB>(fin, w, [&](const FIN &f, int c) {
+            if constexpr (NV == 1) f.col(c, tot[0][c]);
+            else f.col(c, tot[0][c], tot[1][c]);
+        });
     } else {
         sum_partials<NV, NB, kFinBlock>(partial, nblk, tot);
-        if (threadIdx.x == 0) fin(tot);
+        if (!st && threadIdx.x == 0) fin(tot);
     }
 }
 
@@ -465,16 +546,12 @@ template <int NB, class FIN>
 __global__ __launch_bounds__(kFinBlock) void fin2_kernel(const double *__restrict__ pa, int na,
                                                          const double *__restrict__ pb, int nb, FIN fin,
                                                          const int *__restrict__ stop) {
-    if (stop && *stop) return;
     __shared__ double ta[1][NB], tb[1][NB];
-    if constexpr (fin_has_sc<FIN>::value) {
-        const unsigned long long w = sc_stage_load(fin.sc);
-        sum_partials2<NB, kFinBlock>(pa, na, pb, nb, ta, tb);
-        fin_staged(fin, w, [&](const FIN &f) { f(ta, tb); });
-    } else {
-        sum_partials2<NB, kFinBlock>(pa, na, pb, nb, ta, tb);
-        if (threadIdx.x == 0) fin(ta, tb);
-    }
+    const int st = stop ? *stop : 0;
+    const unsigned long long w = sc_stage_load(fin.sc);
+    sum_partials2<NB, kFinBlock>(pa, na, pb, nb, ta, tb);
+    if (st) return;
+    fin_staged<NB>(fin, w, [&](const FIN &f, int c) { f.col(c, ta[0][c], tb[0][c]); });
 }
 
 struct NoFin {
@@ -487,17 +564,28 @@ struct NoFin {
 // FINE = 1 marks launches on the finest level (a separate instantiation, so that
 // profiles separate the fine-level kernels from the coarse-level ones).
 template <typename T, int NB, int NV, class GX, class EP, int FINE, class PRO = NoPro>
-__global__ __launch_bounds__(kBlock) void spmv_kernel(int nrows, const int *__restrict__ rp,
-                                                      const int *__restrict__ ci,
-                                                      const T *__restrict__ av, GX gx, EP ep, Geo geo,
-                                                      Reducer<(NV > 0 ? NV : 1), NB> red,
-                                                      const int *__restrict__ stop, PRO pro = PRO{}) {
-    if (stop && *stop) return;
+__global__ __launch_bounds__(kBlock) void spmv_kernel(const int *__restrict__ stop, int un, int urun, int ustep,
+                                                      int nrows, int lg, const int *__restrict__ rp,
+                                                      const int *__restrict__ ci, const T *__restrict__ av, GX gx,
+                                                      EP ep, Reducer<(NV > 0 ? NV : 1), NB> red, PRO pro = PRO{}) {
     constexpr int CV = spmv_cv<NB>(), NG = NB / CV;
+    const Geo geo = geo_from_lg<NB>(lg);
     const int t = threadIdx.x;
-    const int LPR = geo.lpr(), RPB = geo.rpb(), G = 1 << geo.lg;
+    const int LPR = geo.lpr(), G = 1 << geo.lg;
     const int lane = t & (LPR - 1), c0 = (lane % NG) * CV, g = lane / NG, rl = t >> geo.llpr;
-    const Share sh = xcd_share(ceil_div_dev(nrows, RPB));
+    const Share sh = xcd_share(un, urun, ustep);
+    // the first block's row pointers beside the stop flag (a fused finalize
+    // stops by itself)
+    int row = sh.first * geo.rpb() + rl;
+    int p0 = rp[min(row, nrows - 1)], p1 = rp[min(row, nrows - 1) + 1];
+    if constexpr (!PRO::active) {
+        const int st = *stop;
+        pin_s(st);
+        pin_args(gx);
+        pin_args(ep);
+        pin_v(p0, p1);
+        if (st) return;
+    }
     GX gxv[CV];
     EP epv[CV];
 #pragma unroll
@@ -524,7 +612,6 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(int nrows, const int *__re
         for (int q = 0; q < NVA; ++q) acc[v][q] = 0.0;
     constexpr int U = kSpmvUnroll;  // entries per lane issued together
     for (int blk = sh.first; blk < sh.end; blk += sh.step) {
-        const int row = blk * RPB + rl;
         const bool live = row < nrows;
         typename EP::P pr[CV];
         if (live && g == 0) {
@@ -534,9 +621,11 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(int nrows, const int *__re
         T sum[CV];
 #pragma unroll
         for (int v = 0; v < CV; ++v) sum[v] = T(0);
+        // the next block's row pointers arrive while this one's entries do
+        const int nrow = (blk + sh.step) * geo.rpb() + rl, nr = min(nrow, nrows - 1);
+        const int n0 = rp[nr], n1 = rp[nr + 1];
         if (live) {
-            const int p1 = rp[row + 1];
-            for (int p = rp[row] + g; p < p1; p += U * G) {
+            for (int p = p0 + g; p < p1; p += U * G) {
                 // unconditional loads (past the row's end: its last entry,
                 // weighted by 0), so all U loads and gathers are in flight together
                 int kk[U];
@@ -556,14 +645,15 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(int nrows, const int *__re
                 }
             }
         }
-        for (int off = NG; off < LPR; off <<= 1) {
 #pragma unroll
-            for (int v = 0; v < CV; ++v) sum[v] += __shfl_xor(sum[v], off);
-        }
+        for (int v = 0; v < CV; ++v) sum[v] = group_add<NG>(sum[v], LPR);
         if (live && g == 0) {
 #pragma unroll
             for (int v = 0; v < CV; ++v) epv[v](row, c0 + v, sum[v], pr[v], acc[v]);
         }
+        row = nrow;
+        p0 = n0;
+        p1 = n1;
     }
     if constexpr (NV > 0) block_partials_cv<NV, NB, CV>(acc, red);
 }
@@ -579,15 +669,26 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(int nrows, const int *__re
 template <int NB> constexpr int sell_slices() { return kBlock / (NB / spmv_cv<NB>()) / 64; }  // per workgroup
 
 template <typename T, int NB, int NV, class GX, class EP, class PRO = NoPro, int U = 16>
-__global__ __launch_bounds__(kBlock) void sell_kernel(int nrows, int nsl, const int *__restrict__ soff,
+__global__ __launch_bounds__(kBlock) void sell_kernel(const int *__restrict__ stop, int un, int urun, int ustep,
+                                                      int nrows, int nsl, const int *__restrict__ soff,
                                                       const int *__restrict__ sbase,
                                                       const uint16_t *__restrict__ cd, const T *__restrict__ av, GX gx,
-                                                      EP ep, Reducer<(NV > 0 ? NV : 1), NB> red,
-                                                      const int *__restrict__ stop, PRO pro = PRO{}, int xrot = 0) {
-    if (stop && *stop) return;
+                                                      EP ep, Reducer<(NV > 0 ? NV : 1), NB> red, PRO pro = PRO{},
+                                                      int xrot = 0) {
     constexpr int CV = spmv_cv<NB>(), NG = NB / CV, SPB = sell_slices<NB>();
     const int c0 = (threadIdx.x % NG) * CV, rl = threadIdx.x / NG, lane = rl & 63;
-    const Share sh = xcd_share(ceil_div_dev(nsl, SPB), xrot);
+    const Share sh = xcd_share(un, urun, ustep, xrot);
+    // one slice per wavefront; the first one's place beside the stop flag
+    const int wsl = __builtin_amdgcn_readfirstlane(rl >> 6);
+    int sl = sh.first * SPB + wsl;
+    int o = soff[min(sl, nsl - 1)], oe = soff[min(sl, nsl - 1) + 1], cb = sbase[min(sl, nsl - 1)];
+    if constexpr (!PRO::active) {
+        const int st = *stop;
+        pin_s(st, o, oe, cb);
+        pin_args(gx);
+        pin_args(ep);
+        if (st) return;
+    }
     GX gxv[CV];
     EP epv[CV];
 #pragma unroll
@@ -613,7 +714,6 @@ __global__ __launch_bounds__(kBlock) void sell_kernel(int nrows, int nsl, const 
 #pragma unroll
         for (int q = 0; q < NVA; ++q) acc[v][q] = 0.0;
     for (int blk = sh.first; blk < sh.end; blk += sh.step) {
-        const int sl = blk * SPB + __builtin_amdgcn_readfirstlane(rl >> 6);  // one slice per wavefront
         if (SPB > 1 && sl >= nsl) break;
         const int row = sl * 64 + lane;
         const bool live = row < nrows;
@@ -621,7 +721,9 @@ __global__ __launch_bounds__(kBlock) void sell_kernel(int nrows, int nsl, const 
         if (live)
 #pragma unroll
             for (int v = 0; v < CV; ++v) pr[v] = epv[v].load(row, c0 + v);
-        const int o = soff[sl], w = (soff[sl + 1] - o) >> 6, cb = sbase[sl];
+        const int w = (oe - o) >> 6;
+        const int nsli = (blk + sh.step) * SPB + wsl, nx = min(nsli, nsl - 1);
+        const int no = soff[nx], noe = soff[nx + 1], ncb = sbase[nx];
         T sum[CV];
 #pragma unroll
         for (int v = 0; v < CV; ++v) sum[v] = T(0);
@@ -648,18 +750,21 @@ __global__ __launch_bounds__(kBlock) void sell_kernel(int nrows, int nsl, const 
         if (live)
 #pragma unroll
             for (int v = 0; v < CV; ++v) epv[v](row, c0 + v, sum[v], pr[v], acc[v]);
+        sl = nsli;
+        o = no;
+        oe = noe;
+        cb = ncb;
     }
     if constexpr (NV > 0) block_partials_cv<NV, NB, CV>(acc, red);
 }
 
 // Elementwise kernel over n rows x NB columns with fused reductions.
 template <int NB, int NV, class OP, int FINE>
-__global__ __launch_bounds__(kBlock) void elem_kernel(int n, OP op, Reducer<(NV > 0 ? NV : 1), NB> red,
-                                                      const int *__restrict__ stop) {
-    if (stop && *stop) return;
+__global__ __launch_bounds__(kBlock) void elem_kernel(int un, int urun, int ustep, int n, OP op,
+                                                      Reducer<(NV > 0 ? NV : 1), NB> red) {
     const int t = threadIdx.x, c = t % NB;
     const long total = (long)n * NB;
-    const Share sh = xcd_share((int)ceil_div_dev_l(total, kBlock));
+    const Share sh = xcd_share(un, urun, ustep);
     op.prep(c);
     constexpr int NVA = NV > 0 ? NV : 1;
     double acc[NVA];
@@ -676,24 +781,25 @@ __global__ __launch_bounds__(kBlock) void elem_kernel(int n, OP op, Reducer<(NV 
 // operator kernel (same fixed order in all workgroups, so all agree on alpha),
 // then x += alpha p, r -= alpha q (Jacobi: z = dinv r) on the live columns,
 // with the partials of r.r (and r.z).  Workgroup 0 records alpha and flags a
-// non-positive p.q (breakdown, or indefiniteness for the outer CG).
+// non-positive p.q (breakdown, or indefiniteness for the outer CG).  A CG whose
+// columns have all stopped updates nothing (its scalars say so), so no stop
+// flag is waited for; p, q and r of a thread's first element, which do not
+// depend on alpha, are loaded behind the partials and beside their sums.
 template <typename T, int NB, bool JAC, int FINE>
-__global__ __launch_bounds__(kBlock) void cg_update_kernel(int n, T *__restrict__ x, T *__restrict__ r,
+__global__ __launch_bounds__(kBlock) void cg_update_kernel(int un, int urun, int ustep, int n, int nblk_pq, int fused,
+                                                           T *__restrict__ x, T *__restrict__ r,
+                                                           const T *__restrict__ p, const T *__restrict__ q,
+                                                           CgScal *sc, const double *__restrict__ part_pq,
                                                            T *__restrict__ z, float *__restrict__ r32,
                                                            float *__restrict__ x32, const float *__restrict__ d32,
-                                                           double s0, int fused,
-                                                           const T *__restrict__ p,
-                                                           const T *__restrict__ q, const T *__restrict__ dinv,
-                                                           CgScal *sc, const double *__restrict__ part_pq,
-                                                           int nblk_pq, int outer,
-                                                           Reducer<JAC ? 2 : 1, NB> red,
-                                                           const int *__restrict__ stop) {
-    if (stop && *stop) return;
-    if (!x) x = static_cast<T *>(sc->xptr);
+                                                           double s0, const T *__restrict__ dinv, int outer,
+                                                           Reducer<JAC ? 2 : 1, NB> red) {
     __shared__ double pq[1][NB];
     __shared__ double sh_a[NB];
     __shared__ int sh_live[NB];
     const int t = threadIdx.x;
+    const long total = (long)n * NB;
+    const Share sh = xcd_share(un, urun, ustep);
     // the column's scalars, loaded before the partial sums so that both loads
     // are in flight together (workgroup 0 writes only fields read here by no one)
     int conv0 = 0;
@@ -702,7 +808,16 @@ __global__ __launch_bounds__(kBlock) void cg_update_kernel(int n, T *__restrict_
         conv0 = sc->s[t].conv;
         rho0 = fused ? sc->s[t].rho_next : sc->s[t].rho;
     }
-    if (nblk_pq > 0) sum_partials<1, NB>(part_pq, nblk_pq, pq);
+    T *xx = x ? x : static_cast<T *>(sc->xptr);
+    const size_t of = std::min<size_t>((size_t)sh.first * kBlock + t, total - 1);
+    T pf, qf, rf;
+    auto first = [&] {
+        pf = p[of];
+        qf = q[of];
+        rf = r[of];
+    };
+    if (nblk_pq > 0) sum_partials<1, NB>(part_pq, nblk_pq, pq, first);
+    else first();
     if (nblk_pq == 0) {
         // alpha was formed by a finalize kernel (many partials)
         if (t < NB) {
@@ -727,39 +842,41 @@ __global__ __launch_bounds__(kBlock) void cg_update_kernel(int n, T *__restrict_
         }
         sh_a[t] = a;
         sh_live[t] = live;
-        if (blockIdx.x == 0) {
+        if (blockIdx.x == 0 && !conv0) {
             s.alpha = a;
             s.pq = v;
-            if (fused && !conv0) s.rho = rho0;
+            if (fused) s.rho = rho0;
         }
     }
     __syncthreads();
     const int c = t % NB;
     const T a = (T)sh_a[c];
     const int live = sh_live[c];
-    const long total = (long)n * NB;
-    const Share sh = xcd_share((int)ceil_div_dev_l(total, kBlock));
     double acc[JAC ? 2 : 1] = {};
     if (live) {
         for (int blk = sh.first; blk < sh.end; blk += sh.step) {
             const size_t o = (size_t)blk * kBlock + t;
             if ((long)o >= total) break;
-            const size_t e = o;
-            x[o] += a * p[o];
-            const T rv = r[o] - a * q[o];
+            if (blk != sh.first) {
+                pf = p[o];
+                qf = q[o];
+                rf = r[o];
+            }
+            xx[o] += a * pf;
+            const T rv = rf - a * qf;
             r[o] = rv;
             acc[0] += (double)rv * (double)rv;
             if constexpr (JAC) {
-                const T zz = dinv[e / NB] * rv;
+                const T zz = dinv[o / NB] * rv;
                 z[o] = zz;
                 acc[1] += (double)rv * (double)zz;
             } else {
                 // the V-cycle's first pre-sweep iterate x0 = D^{-1} r (in its precision)
-                if (z) z[o] = (dinv[e / NB] * rv) * (T)s0;
+                if (z) z[o] = (dinv[o / NB] * rv) * (T)s0;
                 if (r32) {
-                    const float rf = (float)rv;
-                    r32[o] = rf;
-                    if (x32) x32[o] = (d32[e / NB] * rf) * (float)s0;
+                    const float rs = (float)rv;
+                    r32[o] = rs;
+                    if (x32) x32[o] = (d32[o / NB] * rs) * (float)s0;
                 }
             }
         }
@@ -973,16 +1090,25 @@ template <typename T, int NB, bool DOT> struct EPost {
 // contiguous values; the epilogue receives both sums.  Columns are int32 or,
 // when the coarse level has at most 65536 nodes, 16-bit (CI = uint16_t).
 template <typename T, int NB, int NV, class EP, typename CI = int>
-__global__ __launch_bounds__(kBlock) void tpro_kernel(int nrows, const int *__restrict__ rp,
+__global__ __launch_bounds__(kBlock) void tpro_kernel(const int *__restrict__ stop, int un, int urun, int ustep,
+                                                      int nrows, int lg, const int *__restrict__ rp,
                                                       const CI *__restrict__ ci, const T *__restrict__ tv,
                                                       const T *__restrict__ sv, const T *__restrict__ e, EP ep,
-                                                      Geo geo, Reducer<(NV > 0 ? NV : 1), NB> red,
-                                                      const int *__restrict__ stop) {
-    if (stop && *stop) return;
+                                                      Reducer<(NV > 0 ? NV : 1), NB> red) {
     constexpr int CV = spmv_cv<NB>(), NG = NB / CV;
-    const int t = threadIdx.x, LPR = geo.lpr(), RPB = geo.rpb(), G = 1 << geo.lg;
+    const Geo geo = geo_from_lg<NB>(lg);
+    const int t = threadIdx.x, LPR = geo.lpr(), G = 1 << geo.lg;
     const int lane = t & (LPR - 1), c0 = (lane % NG) * CV, g = lane / NG, rl = t >> geo.llpr;
-    const Share sh = xcd_share(ceil_div_dev(nrows, RPB));
+    const Share sh = xcd_share(un, urun, ustep);
+    int row = sh.first * geo.rpb() + rl;
+    int p0 = rp[min(row, nrows - 1)], p1 = rp[min(row, nrows - 1) + 1];
+    {
+        const int st = *stop;
+        pin_s(st);
+        pin_args(ep);
+        pin_v(p0, p1);
+        if (st) return;
+    }
     EP epv = ep;
     epv.prep(c0);  // the epilogues of this kernel hold nothing per column
     constexpr int NVA = NV > 0 ? NV : 1;
@@ -993,7 +1119,6 @@ __global__ __launch_bounds__(kBlock) void tpro_kernel(int nrows, const int *__re
         for (int q = 0; q < NVA; ++q) acc[v][q] = 0.0;
     constexpr int U = kSpmvUnroll;
     for (int blk = sh.first; blk < sh.end; blk += sh.step) {
-        const int row = blk * RPB + rl;
         const bool live = row < nrows;
         typename EP::P pr[CV];
         if (live && g == 0) {
@@ -1003,9 +1128,10 @@ __global__ __launch_bounds__(kBlock) void tpro_kernel(int nrows, const int *__re
         T se[CV], te[CV];
 #pragma unroll
         for (int v = 0; v < CV; ++v) se[v] = te[v] = T(0);
+        const int nrow = (blk + sh.step) * geo.rpb() + rl, nr = min(nrow, nrows - 1);
+        const int n0 = rp[nr], n1 = rp[nr + 1];
         if (live) {
-            const int p1 = rp[row + 1];
-            for (int p = rp[row] + g; p < p1; p += U * G) {
+            for (int p = p0 + g; p < p1; p += U * G) {
                 // unconditional loads, as in spmv_kernel
                 int kk[U];
                 T ta[U], sa[U];
@@ -1028,17 +1154,18 @@ __global__ __launch_bounds__(kBlock) void tpro_kernel(int nrows, const int *__re
                     }
             }
         }
-        for (int off = NG; off < LPR; off <<= 1) {  // the G groups of a row and column group
 #pragma unroll
-            for (int v = 0; v < CV; ++v) {
-                se[v] += __shfl_xor(se[v], off);
-                te[v] += __shfl_xor(te[v], off);
-            }
+        for (int v = 0; v < CV; ++v) {  // the G groups of a row and column group
+            se[v] = group_add<NG>(se[v], LPR);
+            te[v] = group_add<NG>(te[v], LPR);
         }
         if (live && g == 0) {
 #pragma unroll
             for (int v = 0; v < CV; ++v) epv(row, c0 + v, se[v], te[v], pr[v], acc[v]);
         }
+        row = nrow;
+        p0 = n0;
+        p1 = n1;
     }
     if constexpr (NV > 0) block_partials_cv<NV, NB, CV>(acc, red);
 }
@@ -1194,55 +1321,42 @@ template <int NB> struct EResid {
 };
 
 // ---------------------------------------------------------------------------
-// finalize steps (thread 0 of the last workgroup)
+// finalize steps
 template <int NB> struct FinAlpha {  // alpha = rho / p.q on live columns
     CgScal *sc;
     int outer;  // 1: flag indefiniteness instead of treating it as breakdown
     int fused;  // 1: rho is the rho_next of the fused finalize, committed here
-    __device__ void operator()(double (&tot)[1][NB]) const {
-        for (int c = 0; c < NB; ++c) {
-            ColScal &s = sc->s[c];
-            if (fused && !s.conv) s.rho = s.rho_next;
-            s.pq = tot[0][c];
-            if (s.conv) {
-                s.alpha = 0.0;
-                continue;
-            }
-            if (!(s.pq > 0.0)) {
-                s.alpha = 0.0;
-                s.bad = 1;
-                if (outer) sc->indefinite = 1;
-                s.conv = 1;
-                continue;
-            }
-            s.alpha = s.rho / s.pq;
+    __device__ void head() const {}
+    __device__ void col(int c, double pq) const {
+        ColScal &s = sc->s[c];
+        if (fused && !s.conv) s.rho = s.rho_next;
+        s.pq = pq;
+        s.alpha = 0.0;
+        if (s.conv) return;
+        if (!(pq > 0.0)) {
+            s.bad = 1;
+            if (outer) sc->indefinite = 1;
+            s.conv = 1;
+            return;
         }
-        int all = 1;
-        for (int c = 0; c < NB; ++c) all &= sc->s[c].conv;
-        publish(sc, NB);
+        s.alpha = s.rho / pq;
     }
 };
 
 template <int NB, bool JAC> struct FinUpd {  // convergence test on r.r (and Jacobi beta)
     CgScal *sc;
-    __device__ void operator()(double (&tot)[JAC ? 2 : 1][NB]) const {
-        int all = 1;
-        for (int c = 0; c < NB; ++c) {
-            ColScal &s = sc->s[c];
-            if (!s.conv) {
-                s.iters += 1;
-                s.rr = tot[0][c];
-                if (s.rr <= s.tol2 || s.bad) s.conv = 1;
-                if constexpr (JAC) {
-                    const double rz = tot[1][c];
-                    s.rz = rz;
-                    s.beta = s.conv ? 0.0 : rz / s.rho;
-                    s.rho = rz;
-                }
-            }
-            all &= s.conv;
+    __device__ void head() const {}
+    __device__ void col(int c, double rr, double rz = 0.0) const {
+        ColScal &s = sc->s[c];
+        if (s.conv) return;
+        s.iters += 1;
+        s.rr = rr;
+        if (rr <= s.tol2 || s.bad) s.conv = 1;
+        if constexpr (JAC) {
+            s.rz = rz;
+            s.beta = s.conv ? 0.0 : rz / s.rho;
+            s.rho = rz;
         }
-        publish(sc, NB);
     }
 };
 
@@ -1251,83 +1365,64 @@ template <int NB, bool JAC> struct FinUpd {  // convergence test on r.r (and Jac
 // the V-cycle's last kernel).
 template <int NB> struct FinUB {
     CgScal *sc;
-    __device__ void operator()(double (&rr)[1][NB], double (&rz)[1][NB]) const {
-        int all = 1;
-        for (int c = 0; c < NB; ++c) {
-            ColScal &s = sc->s[c];
-            if (!s.conv) {
-                s.iters += 1;
-                s.rr = rr[0][c];
-                if (s.bad || s.rr <= s.tol2) {
-                    s.conv = 1;
-                    s.beta = 0.0;
-                } else {
-                    const double v = rz[0][c];
-                    if (!(v > 0.0)) {
-                        s.bad = 1;
-                        s.conv = 1;
-                    } else {
-                        s.rz = v;
-                        s.beta = v / s.rho;
-                        s.rho = v;
-                    }
-                }
-            }
-            all &= s.conv;
+    __device__ void head() const {}
+    __device__ void col(int c, double rr, double rz) const {
+        ColScal &s = sc->s[c];
+        if (s.conv) return;
+        s.iters += 1;
+        s.rr = rr;
+        if (s.bad || rr <= s.tol2) {
+            s.conv = 1;
+            s.beta = 0.0;
+        } else if (!(rz > 0.0)) {
+            s.bad = 1;
+            s.conv = 1;
+        } else {
+            s.rz = rz;
+            s.beta = rz / s.rho;
+            s.rho = rz;
         }
-        publish(sc, NB);
     }
 };
 
 // Inner V-cycle CG start: rho = r.z of the first preconditioner application.
 template <int NB> struct FinRho0 {
     CgScal *sc;
-    __device__ void operator()(double (&tot)[1][NB]) const {
-        int all = 1;
-        for (int c = 0; c < NB; ++c) {
-            ColScal &s = sc->s[c];
-            s.beta = 0.0;
-            if (!s.conv) {
-                const double v = tot[0][c];
-                if (!(v > 0.0)) {
-                    s.bad = 1;
-                    s.conv = 1;
-                } else {
-                    s.rho = v;
-                    s.rz = v;
-                }
-            }
-            all &= s.conv;
+    __device__ void head() const {}
+    __device__ void col(int c, double rz) const {
+        ColScal &s = sc->s[c];
+        s.beta = 0.0;
+        if (s.conv) return;
+        if (!(rz > 0.0)) {
+            s.bad = 1;
+            s.conv = 1;
+        } else {
+            s.rho = rz;
+            s.rz = rz;
         }
-        publish(sc, NB);
     }
 };
 
 template <int NB> struct FinBeta {  // beta = r.z / rho after the preconditioner
     CgScal *sc;
     int outer;
-    __device__ void operator()(double (&tot)[1][NB]) const {
-        for (int c = 0; c < NB; ++c) {
-            ColScal &s = sc->s[c];
-            if (s.conv) {
-                s.beta = 0.0;
-                continue;
-            }
-            const double rz = tot[0][c];
-            if (!(rz > 0.0)) {
-                s.bad = 1;
-                if (outer) sc->indefinite = 1;
-                s.conv = 1;
-                s.beta = 0.0;
-                continue;
-            }
-            s.rz = rz;
-            s.beta = rz / s.rho;
-            s.rho = rz;
+    __device__ void head() const {}
+    __device__ void col(int c, double rz) const {
+        ColScal &s = sc->s[c];
+        if (s.conv) {
+            s.beta = 0.0;
+            return;
         }
-        int all = 1;
-        for (int c = 0; c < NB; ++c) all &= sc->s[c].conv;
-        publish(sc, NB);
+        if (!(rz > 0.0)) {
+            s.bad = 1;
+            if (outer) sc->indefinite = 1;
+            s.conv = 1;
+            s.beta = 0.0;
+            return;
+        }
+        s.rz = rz;
+        s.beta = rz / s.rho;
+        s.rho = rz;
     }
 };
 
@@ -1336,32 +1431,27 @@ template <int NB> struct FinBeta {  // beta = r.z / rho after the preconditioner
 // by FinOuterInit from b.z), else beta = r.z / rho
 template <int NB> struct FinRzConv {
     CgScal *sc;
-    __device__ void operator()(double (&tot)[1][NB]) const {
-        for (int c = 0; c < NB; ++c) {
-            ColScal &s = sc->s[c];
-            if (s.conv) {
-                s.beta = 0.0;
-                continue;
-            }
-            const double rz = tot[0][c];
-            s.iters += 1;
-            s.rz = rz;
-            s.rr = rz;
-            if (s.bad || rz <= s.tol2) {
-                s.conv = 1;
-                s.beta = 0.0;
-                continue;
-            }
-            if (!(rz > 0.0)) {
-                s.bad = 1;
-                s.conv = 1;
-                s.beta = 0.0;
-                continue;
-            }
+    __device__ void head() const {}
+    __device__ void col(int c, double rz) const {
+        ColScal &s = sc->s[c];
+        if (s.conv) {
+            s.beta = 0.0;
+            return;
+        }
+        s.iters += 1;
+        s.rz = rz;
+        s.rr = rz;
+        if (s.bad || rz <= s.tol2) {
+            s.conv = 1;
+            s.beta = 0.0;
+        } else if (!(rz > 0.0)) {
+            s.bad = 1;
+            s.conv = 1;
+            s.beta = 0.0;
+        } else {
             s.beta = rz / s.rho;
             s.rho = rz;
         }
-        publish(sc, NB);
     }
 };
 
@@ -1372,33 +1462,30 @@ template <int NB, bool JAC> struct FinInit {
     int nlive;
     void *x;
     int fused;  // the first fused finalize then gives beta = 0, rho_next = r.z and iteration 0
-    __device__ void operator()(double (&tot)[JAC ? 2 : 1][NB]) const {
+    __device__ void head() const {
         sc->xptr = x;
         sc->nb = nlive;
-        int all = 1;
-        for (int c = 0; c < NB; ++c) {
-            ColScal &s = sc->s[c];
-            s.bb = tot[0][c];
-            s.tol2 = rtol * rtol * s.bb;
-            s.rr = s.bb;
-            s.iters = 0;
-            s.bad = 0;
-            s.alpha = 0.0;
-            s.beta = 0.0;
-            s.rho = 1.0;
-            s.conv = (c >= sc->nb) || !(s.bb > 0.0);
-            if constexpr (JAC) {
-                s.rz = tot[1][c];
-                s.rho = s.conv ? 1.0 : s.rz;
-            }
-            if (fused) {
-                s.rho = __builtin_huge_val();
-                s.iters = -1;
-            }
-            all &= s.conv;
-        }
-        publish(sc, NB);
         sc->indefinite = 0;
+    }
+    __device__ void col(int c, double bb, double rz = 0.0) const {
+        ColScal &s = sc->s[c];
+        s.bb = bb;
+        s.tol2 = rtol * rtol * bb;
+        s.rr = bb;
+        s.iters = 0;
+        s.bad = 0;
+        s.alpha = 0.0;
+        s.beta = 0.0;
+        s.rho = 1.0;
+        s.conv = c >= nlive || !(bb > 0.0);
+        if constexpr (JAC) {
+            s.rz = rz;
+            s.rho = s.conv ? 1.0 : rz;
+        }
+        if (fused) {
+            s.rho = __builtin_huge_val();
+            s.iters = -1;
+        }
     }
 };
 
@@ -1627,42 +1714,36 @@ template <int NB> struct FinOuterInit {
     CgScal *sc;
     double rtol;
     int nlive;
-    __device__ void operator()(double (&tot)[2][NB]) const {
+    __device__ void head() const {
         sc->nb = nlive;
         sc->indefinite = 0;
-        int all = 1;
-        for (int c = 0; c < NB; ++c) {
-            ColScal &s = sc->s[c];
-            s.bb = tot[0][c];
-            s.rr = tot[1][c];
-            s.tol2 = rtol * rtol * s.bb;
-            s.iters = 0;
-            s.bad = 0;
-            s.alpha = s.beta = 0.0;
-            s.rho = 1.0;
-            s.conv = (c >= nlive) || !(s.bb > 0.0) || s.rr <= s.tol2;
-            all &= s.conv;
-        }
-        publish(sc, NB);
+    }
+    __device__ void col(int c, double bb, double rr) const {
+        ColScal &s = sc->s[c];
+        s.bb = bb;
+        s.rr = rr;
+        s.tol2 = rtol * rtol * bb;
+        s.iters = 0;
+        s.bad = 0;
+        s.alpha = s.beta = 0.0;
+        s.rho = 1.0;
+        s.conv = c >= nlive || !(bb > 0.0) || rr <= s.tol2;
     }
 };
 
 template <int NB> struct FinRho {  // rho = r.z at the start of the outer CG
     CgScal *sc;
-    __device__ void operator()(double (&tot)[1][NB]) const {
-        for (int c = 0; c < NB; ++c) {
-            ColScal &s = sc->s[c];
-            if (s.conv) continue;
-            const double rz = tot[0][c];
-            if (!(rz > 0.0)) {
-                s.bad = 1;
-                sc->indefinite = 1;
-                continue;
-            }
-            s.rho = rz;
-            s.rz = rz;
+    __device__ void head() const {}
+    __device__ void col(int c, double rz) const {
+        ColScal &s = sc->s[c];
+        if (s.conv) return;
+        if (!(rz > 0.0)) {
+            s.bad = 1;
+            sc->indefinite = 1;
+            return;
         }
-        publish(sc, NB);
+        s.rho = rz;
+        s.rz = rz;
     }
 };
 
@@ -1735,86 +1816,83 @@ template <> struct Vec16<float> {
 // One column with b of the matrix's type and 16-byte aligned: b is read in the
 // same 16-byte vectors as the matrix rows, eight vectors of each in flight per
 // lane (a float32 row of up to 2048 entries is one round).  Every load is
-// unconditional (guarded loads compile to a wait each): matrix vectors past the
-// row's stride ld re-read its last vector and are zeroed, b vectors past its
-// last full vector re-read that one and are zeroed, and the ragged last vector
-// of b (b is not padded; the rows are zero-padded to ld) is read once per launch
-// with clamped indices.  The products and their order are those of a guarded
-// loop.
+// unconditional (guarded loads compile to a wait each): vectors past the row's
+// stride ld re-read its last vector, and entries past n are zeroed in both.  The
+// last vector of b may reach past its n entries, within the 256-byte granule
+// that every workspace vector is allocated in.  The stop flag is tested before
+// the store, so no load waits for it, and the few wavefronts per SIMD of such
+// a launch may use the registers that keep all loads in flight.
 template <typename TM>
-__global__ __launch_bounds__(kBlock) void dense_apply1_kernel(int n, int ld, const TM *__restrict__ inv,
-                                                              const TM *__restrict__ b, TM *__restrict__ x,
-                                                              const int *__restrict__ stop) {
-    if (stop && *stop) return;
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) void dense_apply1_kernel(
+    const int *__restrict__ stop, int n, int ld, const TM *__restrict__ inv, const TM *__restrict__ b,
+    TM *__restrict__ x) {
     using V = Vec16<TM>;
     using VT = typename V::type;
     constexpr int W = V::n, D = 8;
     const int lane = threadIdx.x % 64;
-    const int w = (blockIdx.x * kBlock + threadIdx.x) / 64;
-    const int nw = gridDim.x * kBlock / 64;
-    const int nal = n - n % W;  // b's full vectors end here
-    VT tail;                    // b[nal .. n-1], zeros after
-    {
-        TM t[W];
+    const int i = (blockIdx.x * kBlock + threadIdx.x) / 64;
+    if (i >= n) return;
+    const int st = *stop;
+    const int last = (n - 1) / W * W;  // the vector that holds entry n - 1
+    double acc = 0.0;
+    const TM *row = inv + (size_t)i * ld;
+    for (int k0 = lane * W; k0 < n; k0 += 64 * W * D) {
+        VT m[D], bv[D];
 #pragma unroll
-        for (int e = 0; e < W; ++e) {
-            const TM v = b[min(nal + e, n - 1)];
-            t[e] = nal + e < n ? v : TM(0);
+        for (int u = 0; u < D; ++u) {
+            const int k = min(k0 + u * 64 * W, last);
+            m[u] = *reinterpret_cast<const VT *>(row + k);
+            bv[u] = *reinterpret_cast<const VT *>(b + k);
         }
-        tail = *reinterpret_cast<const VT *>(t);
-    }
-    for (int i = w; i < n; i += nw) {
-        double acc = 0.0;
-        const TM *row = inv + (size_t)i * ld;
-        for (int k0 = lane * W; k0 < n; k0 += 64 * W * D) {
-            VT m[D], bv[D];
+        // keep the scheduler from interleaving the loads with their uses
+        // (it would otherwise issue them one at a time)
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < D; ++u) {
-                const int k = k0 + u * 64 * W;
-                const VT mv = *reinterpret_cast<const VT *>(row + min(k, ld - W));
-                const VT bl = *reinterpret_cast<const VT *>(b + max(min(k, nal - W), 0));
-                m[u] = k < n ? mv : VT{};
-                bv[u] = k < nal ? bl : k == nal ? tail : VT{};
+        for (int u = 0; u < D; ++u)
+#pragma unroll
+            for (int e = 0; e < W; ++e) {
+                const bool on = k0 + u * 64 * W + e < n;
+                acc += (on ? V::get(m[u], e) : 0.0) * (on ? V::get(bv[u], e) : 0.0);
             }
-            // keep the scheduler from interleaving the loads with their uses
-            // (it would otherwise issue them one at a time)
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < D; ++u)
-#pragma unroll
-                for (int e = 0; e < W; ++e) acc += V::get(m[u], e) * V::get(bv[u], e);
-        }
-        for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
-        if (lane == 0) x[i] = (TM)acc;
     }
+    acc = group_add<1>(acc, 64);
+    if (lane == 0 && !st) x[i] = (TM)acc;
 }
 
-// Several columns: x = Inv B on the FP64 matrix cores.  A workgroup forms 16
-// rows by all columns; its 16 wavefronts take the 16-entry chunks of the rows
-// in turn, each chunk four v_mfma_f64_16x16x4f64 (lane l: row l % 16, the
-// entries 4 (l / 16) .. + 3 of the chunk in one 16-byte load per four floats;
+// Several columns: x = Inv B on the FP64 matrix cores.  A workgroup forms `rows`
+// (at most 16) rows by all columns; its 16 wavefronts take the 16-entry chunks
+// of the rows in turn, each chunk four v_mfma_f64_16x16x4f64 (lane l: row l % 16,
+// the entries 4 (l / 16) .. + 3 of the chunk in one 16-byte load per four floats;
 // step e multiplies entry e of each lane, so the matrix operand's k and the
-// batch operand's k are permuted alike), four chunks' loads in flight, and
-// their sums are added through LDS in wavefront order.  The accumulation is
-// FP64 whatever T.  Columns past NB and rows past n are computed from clamped
-// reads and dropped; chunks past the last are zeroed (rows are zero-padded to
-// ld, so the ragged chunk needs only its batch index clamped).  Bound by the
-// matrix's and the batch's traffic into 100 CUs.  n = 1639, float32, 16 columns:
-// 9.7 us against 29.2 us of a wavefront per row on the vector ALUs, whose
-// lanes each read every column of the batch.
+// batch operand's k are permuted alike), eight (float32) or four chunks' loads
+// in flight, and their sums are added through LDS in wavefront order.  The
+// accumulation is FP64 whatever T.  Lanes past `rows`, columns past NB and rows
+// past n are computed from clamped reads and dropped; chunks past the last are
+// zeroed (rows are zero-padded to ld, so the ragged chunk needs only its batch
+// index clamped).  Bound by the latency of the matrix's and the batch's loads:
+// `rows` is what fills the 256 CUs (dense_mm_rows), matrix-core work done for
+// the lanes past it is not what is waited for.  n = 1639, float32, 16 columns:
+// 9.2 us with 8 rows per workgroup, 9.5 us with 16 (103 workgroups), 29.2 us
+// with a wavefront per row on the vector ALUs, whose lanes each read every
+// column of the batch.
+inline int dense_mm_rows(int n) {
+    int r = 1;
+    while (r < 16 && ceil_div(n, r) > 256) r <<= 1;
+    return r;
+}
 constexpr int kMmWaves = 16;
 typedef double mm_v4d __attribute__((ext_vector_type(4)));
 template <typename T, int NB>
-__global__ __launch_bounds__(64 * kMmWaves) void dense_mm_kernel(int n, int ld, const T *__restrict__ inv,
-                                                                 const T *__restrict__ b, T *__restrict__ x,
-                                                                 const int *__restrict__ stop) {
-    if (stop && *stop) return;
+__global__ __launch_bounds__(64 * kMmWaves) void dense_mm_kernel(const int *__restrict__ stop, int n, int ld,
+                                                                 int rows, const T *__restrict__ inv,
+                                                                 const T *__restrict__ b, T *__restrict__ x) {
+    const int st = *stop;  // tested before the store: no load waits for it
     using V = Vec16<T>;
     using VT = typename V::type;
-    constexpr int D = 4;
+    constexpr int D = sizeof(T) == 4 ? 8 : 4;
     const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, kq = (l >> 4) * 4;
-    const int row0 = blockIdx.x * 16;
-    const T *row = inv + (size_t)min(row0 + (l & 15), n - 1) * ld;
+    const int row0 = blockIdx.x * rows;
+    const T *row = inv + (size_t)min(row0 + min(l & 15, rows - 1), n - 1) * ld;
     const int col = min(l & 15, NB - 1);
     const int nk = (n + 15) / 16;
     mm_v4d acc = {0.0, 0.0, 0.0, 0.0};
@@ -1848,8 +1926,8 @@ __global__ __launch_bounds__(64 * kMmWaves) void dense_mm_kernel(int n, int ld, 
     double s = 0.0;
 #pragma unroll
     for (int w = 0; w < kMmWaves; ++w) s += red[w][wv][l];
-    const int i = row0 + (l >> 4) + 4 * wv;  // result r of lane l: row l / 16 + 4 r, column l % 16
-    if (i < n && (l & 15) < NB) x[(size_t)i * NB + (l & 15)] = (T)s;
+    const int k = (l >> 4) + 4 * wv, i = row0 + k;  // result r of lane l: row l / 16 + 4 r, column l % 16
+    if (!st && k < rows && i < n && (l & 15) < NB) x[(size_t)i * NB + (l & 15)] = (T)s;
 }
 
 }  // namespace amg

@@ -72,6 +72,9 @@ template <int NB> struct Solver {
                                pgrid[pbuf], fin, stop);
     }
 
+    // the word a kernel tests before it writes: the CG's flag, or one that stays zero
+    const int *flag(const int *stop) const { return stop ? stop : c.never; }
+
     // workgroups of a reducing product with A (the partials it leaves)
     template <typename T> int red_grid(const DCsr &A) const {
         if (A.sell_for(NB)) return grid_rows(A.nsl, sell_slices<NB>(), red_grid_max<NB>());
@@ -87,27 +90,31 @@ template <int NB> struct Solver {
         else sv = vals == A.v ? A.sl_v : nullptr;
         if (A.sell_for(NB) && sv) {
             const int g = grid_rows(A.nsl, sell_slices<NB>(), NV > 0 ? red_grid_max<NB>() : kMaxGridPlain);
+            const Units u = units(ceil_div(A.nsl, sell_slices<NB>()), g);
             Reducer<(NV > 0 ? NV : 1), NB> red{part[pbuf]};
             if (NV > 0) pgrid[pbuf] = g;
             if (NB > 1 || !A.sl_over8)
-                hipLaunchKernelGGL((sell_kernel<T, NB, NV, GX, EP, PRO, 8>), dim3(g), dim3(kBlock), 0, s, A.n, A.nsl,
-                                   A.sl_off, A.sl_base, A.sl_cd, sv, gx, ep, red, stop, pro, xrot);
+                hipLaunchKernelGGL((sell_kernel<T, NB, NV, GX, EP, PRO, 8>), dim3(g), dim3(kBlock), 0, s, flag(stop),
+                                   u.n, u.run, u.step, A.n, A.nsl, A.sl_off, A.sl_base, A.sl_cd, sv, gx, ep, red, pro,
+                                   xrot);
             else
                 hipLaunchKernelGGL((sell_kernel<T, NB, NV, GX, EP, PRO, NB == 1 ? 16 : 8>), dim3(g), dim3(kBlock), 0,
-                                   s, A.n, A.nsl, A.sl_off, A.sl_base, A.sl_cd, sv, gx, ep, red, stop, pro, xrot);
+                                   s, flag(stop), u.n, u.run, u.step, A.n, A.nsl, A.sl_off, A.sl_base, A.sl_cd, sv, gx,
+                                   ep, red, pro, xrot);
             finish<NV>(pbuf, fin, stop);
             return;
         }
         const Geo geo = geo_for<NB, T>(A);
         const int g = grid_rows(A.n, geo.rpb(), NV > 0 ? red_grid_max<NB>() : kMaxGridPlain);
+        const Units u = units(ceil_div(A.n, geo.rpb()), g);
         Reducer<(NV > 0 ? NV : 1), NB> red{part[pbuf]};
         if (NV > 0) pgrid[pbuf] = g;
         if (A.n == c.N)
-            hipLaunchKernelGGL((spmv_kernel<T, NB, NV, GX, EP, 1, PRO>), dim3(g), dim3(kBlock), 0, s, A.n, A.rp,
-                               A.ci, vals, gx, ep, geo, red, stop, pro);
+            hipLaunchKernelGGL((spmv_kernel<T, NB, NV, GX, EP, 1, PRO>), dim3(g), dim3(kBlock), 0, s, flag(stop), u.n,
+                               u.run, u.step, A.n, geo.lg, A.rp, A.ci, vals, gx, ep, red, pro);
         else
-            hipLaunchKernelGGL((spmv_kernel<T, NB, NV, GX, EP, 0, PRO>), dim3(g), dim3(kBlock), 0, s, A.n, A.rp,
-                               A.ci, vals, gx, ep, geo, red, stop, pro);
+            hipLaunchKernelGGL((spmv_kernel<T, NB, NV, GX, EP, 0, PRO>), dim3(g), dim3(kBlock), 0, s, flag(stop), u.n,
+                               u.run, u.step, A.n, geo.lg, A.rp, A.ci, vals, gx, ep, red, pro);
         finish<NV>(pbuf, fin, stop);
     }
 
@@ -119,24 +126,28 @@ template <int NB> struct Solver {
         c.st.bytes += spmv_bytes(Lv.S.n, Lv.S.nnz, sizeof(T), NB) + spmv_bytes(Lv.A.n, Lv.A.nnz, sizeof(T), NB);
         const Geo geo = geo_for<NB, T>(Tm, true);
         const int g = grid_rows(Tm.n, geo.rpb(), NV > 0 ? red_grid_max<NB>() : kMaxGridPlain);
+        const Units u = units(ceil_div(Tm.n, geo.rpb()), g);
         Reducer<(NV > 0 ? NV : 1), NB> red{part[pbuf]};
         if (NV > 0) pgrid[pbuf] = g;
         if (Lv.Tc16)
-            hipLaunchKernelGGL((tpro_kernel<T, NB, NV, EP, uint16_t>), dim3(g), dim3(kBlock), 0, s, Tm.n, Tm.rp,
-                               Lv.Tc16, avals<T>(Tm), tsvals<T>(Lv), e, ep, geo, red, stop);
+            hipLaunchKernelGGL((tpro_kernel<T, NB, NV, EP, uint16_t>), dim3(g), dim3(kBlock), 0, s, flag(stop), u.n,
+                               u.run, u.step, Tm.n, geo.lg, Tm.rp, Lv.Tc16, avals<T>(Tm), tsvals<T>(Lv), e, ep, red);
         else
-            hipLaunchKernelGGL((tpro_kernel<T, NB, NV, EP>), dim3(g), dim3(kBlock), 0, s, Tm.n, Tm.rp, Tm.ci,
-                               avals<T>(Tm), tsvals<T>(Lv), e, ep, geo, red, stop);
+            hipLaunchKernelGGL((tpro_kernel<T, NB, NV, EP>), dim3(g), dim3(kBlock), 0, s, flag(stop), u.n, u.run,
+                               u.step, Tm.n, geo.lg, Tm.rp, Tm.ci, avals<T>(Tm), tsvals<T>(Lv), e, ep, red);
     }
 
     template <int NV, class OP, class FIN> void elem(int n, OP op, FIN fin, const int *stop, int pbuf = 0) {
         const int g = grid_rows((long)n * NB, kBlock, NV > 0 ? red_grid_max<NB>() : kMaxGridPlain);
         Reducer<(NV > 0 ? NV : 1), NB> red{part[pbuf]};
         if (NV > 0) pgrid[pbuf] = g;
+        const Units u = units(ceil_div((long)n * NB, kBlock), g);
         if (n == c.N)
-            hipLaunchKernelGGL((elem_kernel<NB, NV, OP, 1>), dim3(g), dim3(kBlock), 0, s, n, op, red, stop);
+            hipLaunchKernelGGL((elem_kernel<NB, NV, OP, 1>), dim3(g), dim3(kBlock), 0, s, u.n, u.run, u.step, n, op,
+                               red);
         else
-            hipLaunchKernelGGL((elem_kernel<NB, NV, OP, 0>), dim3(g), dim3(kBlock), 0, s, n, op, red, stop);
+            hipLaunchKernelGGL((elem_kernel<NB, NV, OP, 0>), dim3(g), dim3(kBlock), 0, s, u.n, u.run, u.step, n, op,
+                               red);
         finish<NV>(pbuf, fin, stop);
     }
 
@@ -156,12 +167,13 @@ template <int NB> struct Solver {
             nblk_pq = 0;
         }
         pgrid[1] = g;
-        if (n == c.N)
-            hipLaunchKernelGGL((cg_update_kernel<T, NB, JAC, 1>), dim3(g), dim3(kBlock), 0, s, n, x, r, z, r32, x32, d32, s0, fused, p, q, dinv,
-                               sc, part[0], nblk_pq, outer, red, stop);
-        else
-            hipLaunchKernelGGL((cg_update_kernel<T, NB, JAC, 0>), dim3(g), dim3(kBlock), 0, s, n, x, r, z, r32, x32, d32, s0, fused, p, q, dinv,
-                               sc, part[0], nblk_pq, outer, red, stop);
+        const Units u = units(ceil_div((long)n * NB, kBlock), g);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, s, u.n, u.run, u.step, n, nblk_pq, fused, x, r, p, q,
+                               sc, part[0], z, r32, x32, d32, s0, dinv, outer, red);
+        };
+        if (n == c.N) go(cg_update_kernel<T, NB, JAC, 1>);
+        else go(cg_update_kernel<T, NB, JAC, 0>);
     }
 
     template <typename T> void dense_apply(const DenseOp &d, const T *b, T *x, const int *stop) {
@@ -169,13 +181,13 @@ template <int NB> struct Solver {
         const T *m;
         if constexpr (std::is_same_v<T, float>) m = d.m32;
         else m = d.m64;
-        // the vector kernel reads b in 16-byte vectors: it needs one full vector
-        if (NB == 1 && reinterpret_cast<uintptr_t>(b) % 16 == 0 && d.n * sizeof(T) >= 16)
+        // the vector kernel reads b (a workspace vector) in 16-byte vectors
+        if (NB == 1 && reinterpret_cast<uintptr_t>(b) % 16 == 0)
             hipLaunchKernelGGL((dense_apply1_kernel<T>), dim3(ceil_div((long)d.n * 64, kBlock)), dim3(kBlock), 0, s,
-                               d.n, d.ld, m, b, x, stop);
+                               flag(stop), d.n, d.ld, m, b, x);
         else
-            hipLaunchKernelGGL((dense_mm_kernel<T, NB>), dim3(ceil_div(d.n, 16)), dim3(64 * kMmWaves), 0, s, d.n,
-                               d.ld, m, b, x, stop);
+            hipLaunchKernelGGL((dense_mm_kernel<T, NB>), dim3(ceil_div(d.n, dense_mm_rows(d.n))), dim3(64 * kMmWaves),
+                               0, s, flag(stop), d.n, d.ld, dense_mm_rows(d.n), m, b, x);
     }
 
     void read_sc(const CgScal *d) {
