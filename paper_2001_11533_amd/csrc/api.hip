@@ -370,7 +370,10 @@ template <int NB> int tune_time(Ctx &c, int reps) {
         }
         const int pi = prec == 32 ? 1 : 0, nbi = ilog2(NB);
         const int lgmax = max_lg<NB>();
-        const int lg_def = make_geo<NB>(A.nnz, A.n, is_t && prec == 32).lg;  // the default rule's choice
+        const int lg_def = make_geo<NB>(A.nnz, A.n, is_t && prec == 32,
+                                        !is_t && A.n != c.N &&
+                                            (prec == 32 ? long_rows<NB, float>(A) : long_rows<NB, double>(A)))
+                               .lg;  // the default rule's choice
         auto launch = [&](auto tT) {
             using T = decltype(tT);
             Level &Lv = c.lev[l];

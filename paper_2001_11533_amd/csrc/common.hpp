@@ -207,9 +207,12 @@ struct DCsr {
 constexpr int kBlock = 256;      // threads per workgroup (4 wavefronts of 64)
 constexpr int kMaxGrid = 16384;        // workgroups at most for kernels with reductions
 constexpr int kMaxGridPlain = 1 << 20; // and for kernels without
-// Reducing launches on NB columns: the partials of a finalize grow as grid x NB,
-// so wide batches take fewer (fuller) workgroups.
-template <int NB> constexpr int red_grid_max() { return NB <= 2 ? kMaxGrid : kMaxGrid / NB; }
+// Workgroups of a reducing launch on NB columns at most: about what is resident
+// at once (four per CU at the registers of the FP64 products), each sweeping its
+// share.  Few partials keep the finalize folded into the next product: with up
+// to 16384 workgroups for one column, a CG iteration on 184344 rows took two
+// finalize launches more (4.7 + 4.2 us), one on 2.1e6 rows too.
+template <int NB> constexpr int red_grid_max() { return NB <= 2 ? 1024 : kMaxGrid / NB; }
 constexpr int kFinBlock = 1024;        // threads of a finalize kernel
 constexpr int kXcd = 8;          // XCDs of an MI355X
 

@@ -177,8 +177,19 @@ __host__ __device__ constexpr int ilog2(int x) {
     return l;
 }
 
-// entries a lane loads together
-constexpr int kSpmvUnroll = 4;
+// entries a lane loads together, and in large matrices of long rows
+constexpr int kSpmvUnroll = 4, kSpmvUnrollLong = 8;
+
+// Whether a one-column product on a coarse matrix takes kSpmvUnrollLong entries
+// per lane: rows of more than 16 entries, 10 MB or more of entries.  Such a
+// launch is several rounds of wavefronts per CU, each round as long as its
+// loads' latency, so twice the entries per lane halve the rounds (184344 rows
+// of 46 entries in FP64: 34.2 -> 25.4 us; of 33 in float32: 15.1 -> 12.2 us);
+// a smaller one is a single round that more lanes shorten (22748 rows of 32 in
+// float32: 3.5 us, 3.8 us with eight entries).
+template <int NB, typename T> inline bool long_rows(const DCsr &A) {
+    return NB == 1 && A.nnz > 16L * A.n && (4.0 + sizeof(T)) * (double)A.nnz >= 1e7;
+}
 
 // The fixed rule for G, from the mean row length m (measured over G = 1 .. 64 on
 // every product of 2D and 3D hierarchies of 7e4 to 2.1e6 rows, 1 to 16 columns):
@@ -193,12 +204,12 @@ constexpr int kSpmvUnroll = 4;
 //     over T at 2.1e6 rows: 252 us with G = 1, 266 with 2, 313 with 4); and small
 //     matrices widen G, up to m / 2, until the launch has 2^17 lanes (16 columns
 //     at 1742 rows of 94 entries: 3.5 us with G = 16, 5.3 us with 4).
-template <int NB> inline Geo make_geo(long nnz, long rows, bool t32 = false) {
+template <int NB> inline Geo make_geo(long nnz, long rows, bool t32 = false, bool lrows = false) {
     constexpr int NG = NB / spmv_cv<NB>();
     const double m = rows > 0 ? (double)nnz / (double)rows : 1.0;
     constexpr double per = NB <= 2 ? kSpmvUnroll : NB == 4 ? 6.0 : NB == 8 ? 8.0 : 14.0;
     int g = 1;
-    while (g < 64 && g < m / per) g <<= 1;
+    while (g < 64 && g < m / (lrows ? kSpmvUnrollLong : per)) g <<= 1;
     if (NB <= 8 && m > kSpmvUnroll) g = std::max(g, 2);
     if (NB <= 4 && t32 && m > kSpmvUnroll && m <= 2 * kSpmvUnroll) g = 4;
     if constexpr (NB > 2)
@@ -222,11 +233,11 @@ template <int NB> __host__ __device__ inline Geo geo_from_lg(int lg) {
 template <int NB> constexpr int max_lg() { return NB >= 4 ? 6 - (NB == 4 ? 0 : NB == 8 ? 1 : 2) : 6; }
 
 // the autotuner's choice for this matrix, batch width and value type, else the
-// default rule (is_t: the fused pass over T = A S)
-template <int NB, typename T> inline Geo geo_for(const DCsr &A, bool is_t = false) {
+// default rule (fine: a matrix of the finest level; is_t: the fused pass over T = A S)
+template <int NB, typename T> inline Geo geo_for(const DCsr &A, int fine, bool is_t = false) {
     constexpr bool f32 = std::is_same_v<T, float>;
     const int t = A.tuned_lg[ilog2(NB)][f32 ? 1 : 0];
-    return t >= 0 ? geo_from_lg<NB>(t) : make_geo<NB>(A.nnz, A.n, is_t && f32);
+    return t >= 0 ? geo_from_lg<NB>(t) : make_geo<NB>(A.nnz, A.n, is_t && f32, !is_t && fine == 0 && long_rows<NB, T>(A));
 }
 
 template <int NV, int NB> struct Reducer {
@@ -563,7 +574,7 @@ struct NoFin {
 // functor (what is written for row i); optional fused reductions.
 // FINE = 1 marks launches on the finest level (a separate instantiation, so that
 // profiles separate the fine-level kernels from the coarse-level ones).
-template <typename T, int NB, int NV, class GX, class EP, int FINE, class PRO = NoPro>
+template <typename T, int NB, int NV, class GX, class EP, int FINE, class PRO = NoPro, int U = kSpmvUnroll>
 __global__ __launch_bounds__(kBlock) void spmv_kernel(const int *__restrict__ stop, int un, int urun, int ustep,
                                                       int nrows, int lg, const int *__restrict__ rp,
                                                       const int *__restrict__ ci, const T *__restrict__ av, GX gx,
@@ -610,7 +621,6 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(const int *__restrict__ st
     for (int v = 0; v < CV; ++v)
 #pragma unroll
         for (int q = 0; q < NVA; ++q) acc[v][q] = 0.0;
-    constexpr int U = kSpmvUnroll;  // entries per lane issued together
     for (int blk = sh.first; blk < sh.end; blk += sh.step) {
         const bool live = row < nrows;
         typename EP::P pr[CV];

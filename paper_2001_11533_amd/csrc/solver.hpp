@@ -78,7 +78,7 @@ template <int NB> struct Solver {
     // workgroups of a reducing product with A (the partials it leaves)
     template <typename T> int red_grid(const DCsr &A) const {
         if (A.sell_for(NB)) return grid_rows(A.nsl, sell_slices<NB>(), red_grid_max<NB>());
-        return grid_rows(A.n, geo_for<NB, T>(A).rpb(), red_grid_max<NB>());
+        return grid_rows(A.n, geo_for<NB, T>(A, A.n == c.N).rpb(), red_grid_max<NB>());
     }
 
     template <typename T, int NV, class GX, class EP, class FIN, class PRO = NoPro>
@@ -104,17 +104,18 @@ template <int NB> struct Solver {
             finish<NV>(pbuf, fin, stop);
             return;
         }
-        const Geo geo = geo_for<NB, T>(A);
+        const Geo geo = geo_for<NB, T>(A, A.n == c.N);
         const int g = grid_rows(A.n, geo.rpb(), NV > 0 ? red_grid_max<NB>() : kMaxGridPlain);
         const Units u = units(ceil_div(A.n, geo.rpb()), g);
         Reducer<(NV > 0 ? NV : 1), NB> red{part[pbuf]};
         if (NV > 0) pgrid[pbuf] = g;
-        if (A.n == c.N)
-            hipLaunchKernelGGL((spmv_kernel<T, NB, NV, GX, EP, 1, PRO>), dim3(g), dim3(kBlock), 0, s, flag(stop), u.n,
-                               u.run, u.step, A.n, geo.lg, A.rp, A.ci, vals, gx, ep, red, pro);
-        else
-            hipLaunchKernelGGL((spmv_kernel<T, NB, NV, GX, EP, 0, PRO>), dim3(g), dim3(kBlock), 0, s, flag(stop), u.n,
-                               u.run, u.step, A.n, geo.lg, A.rp, A.ci, vals, gx, ep, red, pro);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, s, flag(stop), u.n, u.run, u.step, A.n, geo.lg, A.rp,
+                               A.ci, vals, gx, ep, red, pro);
+        };
+        if (A.n == c.N) go(spmv_kernel<T, NB, NV, GX, EP, 1, PRO>);
+        else if (long_rows<NB, T>(A)) go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO, NB == 1 ? kSpmvUnrollLong : kSpmvUnroll>);
+        else go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO>);
         finish<NV>(pbuf, fin, stop);
     }
 
@@ -124,7 +125,7 @@ template <int NB> struct Solver {
         const DCsr &Tm = Lv.T;
         // the method's work here: the prolongation S e and the product A (x + S e)
         c.st.bytes += spmv_bytes(Lv.S.n, Lv.S.nnz, sizeof(T), NB) + spmv_bytes(Lv.A.n, Lv.A.nnz, sizeof(T), NB);
-        const Geo geo = geo_for<NB, T>(Tm, true);
+        const Geo geo = geo_for<NB, T>(Tm, Tm.n == c.N, true);
         const int g = grid_rows(Tm.n, geo.rpb(), NV > 0 ? red_grid_max<NB>() : kMaxGridPlain);
         const Units u = units(ceil_div(Tm.n, geo.rpb()), g);
         Reducer<(NV > 0 ? NV : 1), NB> red{part[pbuf]};
