@@ -1395,6 +1395,23 @@ template <int NB> struct FinUB {
     }
 };
 
+// Inner V-cycle CG, between the update and the preconditioner where a column
+// is expected to have converged: the convergence test on r.r alone.  A column
+// that stops here is recorded as the finalize after the preconditioner would
+// record it (that step no longer touches it); the others are left alone.
+template <int NB> struct FinConv {
+    CgScal *sc;
+    __device__ void head() const {}
+    __device__ void col(int c, double rr) const {
+        ColScal &s = sc->s[c];
+        if (s.conv || !(s.bad || rr <= s.tol2)) return;
+        s.iters += 1;
+        s.rr = rr;
+        s.beta = 0.0;
+        s.conv = 1;
+    }
+};
+
 // Inner V-cycle CG start: rho = r.z of the first preconditioner application.
 template <int NB> struct FinRho0 {
     CgScal *sc;

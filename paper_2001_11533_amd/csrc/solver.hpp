@@ -343,8 +343,11 @@ template <int NB> struct Solver {
     // Returns the largest iteration count over the columns; x_out gets x.
     // MIX (FP64 CG only): the preconditioner is the float32 V-cycle; the CG
     // update also writes r in float32 and the next direction reads z from it.
+    // check: test convergence between the update and the preconditioner, so that
+    // the V-cycle that would follow the last update is not run.
     template <typename T, bool JAC, bool MIX = false>
-    void cg_iter(int j, const DCsr &A, const T *vals, const T *dinv, CgWs<T> &w, T *pold, T *pnew) {
+    void cg_iter(int j, const DCsr &A, const T *vals, const T *dinv, CgWs<T> &w, T *pold, T *pnew,
+                 bool check = false) {
         const int n = A.n;
         const int *stop = &w.sc->all_conv;
         const int fused = w.fused;
@@ -360,6 +363,7 @@ template <int NB> struct Solver {
             first(GZ<T, NB, float>{z32}, ECgQR<T, NB, float>{z32, pold, pnew, w.q, w.sc});
             cg_update<T, false>(n, nullptr, w.r, nullptr, pnew, w.q, nullptr, w.sc, 0, stop, r32,
                                 vcws<float>(c.ws[j]).x, c.lev[j].dl1inv32, first_scale(), fused);
+            if (check) finish<1>(1, FinConv<NB>{w.sc}, stop);
             vcycle<float>(j, r32, z32, true, stop);
             if (!fused)
                 hipLaunchKernelGGL((fin2_kernel<NB, FinUB<NB>>), dim3(1), dim3(kFinBlock), 0, s, part[1],
@@ -376,6 +380,7 @@ template <int NB> struct Solver {
         if constexpr (JAC) {
             if (!fused) finish<2>(1, FinUpd<NB, true>{w.sc}, stop);
         } else {
+            if (check) finish<1>(1, FinConv<NB>{w.sc}, stop);
             vcycle<T>(j, w.r, w.z, true, stop);
             if (!fused)
                 hipLaunchKernelGGL((fin2_kernel<NB, FinUB<NB>>), dim3(1), dim3(kFinBlock), 0, s, part[1],
@@ -439,10 +444,10 @@ template <int NB> struct Solver {
             else vcycle<T>(j, w.r, w.z, true, stop);
             if (!fused) finish<1>(2, FinRho0<NB>{w.sc}, stop);
         };
-        // Iterations go out in pairs (p0 -> p1 -> p0), one graph launch per pair,
-        // so the iteration count before a launch is even; a single iteration is
-        // issued only as the last one before maxit.  Iterations past convergence
-        // return at once in every kernel.
+        // Captured iterations go out in pairs (p0 -> p1 -> p0), one graph launch per
+        // pair, so the iteration count before a launch is even; a single iteration is
+        // issued only as the last one before maxit.  Eager iterations go out one by
+        // one.  Iterations past convergence return at once in every kernel.
         if (graphs && !w.g2) {
             if constexpr (!JAC) w.g0 = capture(first_precond);
             w.g2 = capture([&] {
@@ -466,20 +471,27 @@ template <int NB> struct Solver {
             }
         }
         int it = phase == 2 ? w.run_it : 0;
+        // Eager V-cycle CGs test convergence before the preconditioner from the
+        // iteration before the previous solve's last one on (a 5 us launch): the
+        // V-cycle after the last update, and the iteration in which a fused finalize
+        // would find the end, are then not run.
+        const bool checks = !graphs && !JAC;
+        const int pred = w.pred;
         auto step = [&]() {
-            const bool pair = maxit - it >= 2;
-            if (graphs) {
-                if (!pair && !w.ga) w.ga = capture([&] { cg_iter<T, JAC, MIX>(j, A, vals, dinv, w, w.p0, w.p1); });
-                launch(pair ? w.g2 : w.ga);
-            } else {
-                cg_iter<T, JAC, MIX>(j, A, vals, dinv, w, w.p0, w.p1);
-                if (pair) cg_iter<T, JAC, MIX>(j, A, vals, dinv, w, w.p1, w.p0);
+            if (!graphs) {
+                cg_iter<T, JAC, MIX>(j, A, vals, dinv, w, it % 2 ? w.p1 : w.p0, it % 2 ? w.p0 : w.p1,
+                                     checks && it + 2 >= pred);
+                ++it;
+                return;
             }
+            const bool pair = maxit - it >= 2;
+            if (!pair && !w.ga) w.ga = capture([&] { cg_iter<T, JAC, MIX>(j, A, vals, dinv, w, w.p0, w.p1); });
+            launch(pair ? w.g2 : w.ga);
             it += pair ? 2 : 1;
         };
         // The iterations the previous solve at this level needed (one more when
-        // fused: the convergence of update k is decided in iteration k + 1) go
-        // out at once, and the host waits for them: usually they suffice, and
+        // fused and not tested: the convergence of update k is then decided in
+        // iteration k + 1) go out at once, and the host waits for them: usually they suffice, and
         // nothing runs past convergence.  When they do not, the host keeps two
         // launches in flight beyond the last one it has seen (it waits on the
         // older one's event while the newer one runs), reading the mailbox
@@ -488,7 +500,7 @@ template <int NB> struct Solver {
         constexpr int kRing = Ctx::kPollRing;
         int posted = 1, seen = 0;
         if (phase != 2) {
-            const int first = std::min(std::max(1, w.pred + (fused ? 1 : 0) + margin), maxit);
+            const int first = std::min(std::max(1, w.pred + (fused && !checks ? 1 : 0) + margin), maxit);
             while (it < first) {
                 if (graphs && w.g8 && first - it >= 8) {
                     launch(w.g8);
