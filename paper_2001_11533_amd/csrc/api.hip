@@ -163,6 +163,24 @@ double ms_since(clk::time_point t0) {
     return std::chrono::duration<double, std::milli>(clk::now() - t0).count();
 }
 
+// The caller's vectors as [n x NB] ones: used in place when the batch has no
+// padding columns (and an input does not overlap the output), else packed into
+// and unpacked from the context's buffers, a launch and a pass over the vector
+// each.
+template <int NB>
+const double *vec_in(Solver<NB> &S, int n, const double *v, double *buf, int nb, const double *out,
+                     bool in_place = true) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(v), b = reinterpret_cast<uintptr_t>(out);
+    const uintptr_t len = sizeof(double) * (uintptr_t)n * nb;
+    if (in_place && nb == NB && (!out || a + len <= b || b + len <= a)) return v;
+    S.template elem<0>(n, OpPack<NB>{buf, v, nb}, NoFin{}, nullptr);
+    return buf;
+}
+template <int NB> double *vec_out(double *v, double *buf, int nb) { return nb == NB ? v : buf; }
+template <int NB> void vec_done(Solver<NB> &S, int n, double *v, const double *buf, int nb) {
+    if (nb != NB) S.template elem<0>(n, OpUnpack<NB>{v, buf, nb}, NoFin{}, nullptr);
+}
+
 int check_vec_call(Ctx *c, int level, int nb) {
     if (!c) return AMG_ERR_ARG;
     if (level < 0 || level >= c->L) {
@@ -634,9 +652,9 @@ int state_solve(amg_ctx *ctx, int level, const double *u, double *y, int nb, amg
         return dispatch_nb(c.nbp, [&](auto tag) {
             constexpr int NB = decltype(tag)::value;
             Solver<NB> S(c);
-            S.template elem<0>(n, OpPack<NB>{c.pk_in, u, nb}, NoFin{}, nullptr);
-            S.state_solve(level, c.pk_in, c.pk_out, c.o.inner_rtol);
-            S.template elem<0>(n, OpUnpack<NB>{y, c.pk_out, nb}, NoFin{}, nullptr);
+            const double *in = vec_in(S, n, u, c.pk_in, nb, y);
+            S.state_solve(level, in, vec_out<NB>(y, c.pk_out, nb), c.o.inner_rtol);
+            vec_done(S, n, y, c.pk_out, nb);
             AMG_HIP(hipStreamSynchronize(c.stream));
             fill_info(c, info, 1, ms_since(t0), 0);
             return AMG_OK;
@@ -655,9 +673,11 @@ int adjoint_solve(amg_ctx *ctx, int level, const double *w, double *z, int nb, a
         return dispatch_nb(c.nbp, [&](auto tag) {
             constexpr int NB = decltype(tag)::value;
             Solver<NB> S(c);
-            S.template elem<0>(n, OpPack<NB>{c.pk_in, w, nb}, NoFin{}, nullptr);
-            S.adjoint_solve(level, c.pk_in, c.pk_out, c.o.inner_rtol);
-            S.template elem<0>(n, OpUnpack<NB>{z, c.pk_out, nb}, NoFin{}, nullptr);
+            // a dense solve reads its right-hand side in whole vectors, past n
+            const bool dense = level == c.L - 1 || c.lev[level].Ainv;
+            const double *in = vec_in(S, n, w, c.pk_in, nb, z, !dense);
+            S.adjoint_solve(level, in, vec_out<NB>(z, c.pk_out, nb), c.o.inner_rtol);
+            vec_done(S, n, z, c.pk_out, nb);
             AMG_HIP(hipStreamSynchronize(c.stream));
             fill_info(c, info, 1, ms_since(t0), 0);
             return AMG_OK;
@@ -676,9 +696,9 @@ int hessian_apply(amg_ctx *ctx, int level, const double *u, double *Hu, int nb, 
         return dispatch_nb(c.nbp, [&](auto tag) {
             constexpr int NB = decltype(tag)::value;
             Solver<NB> S(c);
-            S.template elem<0>(n, OpPack<NB>{c.pk_in, u, nb}, NoFin{}, nullptr);
-            S.hessian_apply(level, c.pk_in, c.pk_out, c.o.inner_rtol, nullptr);
-            S.template elem<0>(n, OpUnpack<NB>{Hu, c.pk_out, nb}, NoFin{}, nullptr);
+            const double *in = vec_in(S, n, u, c.pk_in, nb, Hu);
+            S.hessian_apply(level, in, vec_out<NB>(Hu, c.pk_out, nb), c.o.inner_rtol, nullptr);
+            vec_done(S, n, Hu, c.pk_out, nb);
             AMG_HIP(hipStreamSynchronize(c.stream));
             fill_info(c, info, 1, ms_since(t0), 0);
             return AMG_OK;
@@ -729,8 +749,7 @@ int reduced_solve(amg_ctx *ctx, const double *yd, const double *u0, double *u, i
             c.ph.mark(kPhRhs, c.stream);
             {
                 Range rr("rhs");
-                S.template elem<0>(n, OpPack<NB>{c.pk_in, yd, nb}, NoFin{}, nullptr);
-                S.mass_apply(0, 1, c.pk_in, c.obq, nullptr, nullptr);
+                S.mass_apply(0, 1, vec_in<NB>(S, n, yd, c.pk_in, nb, nullptr), c.obq, nullptr, nullptr);
                 S.adjoint_solve(0, c.obq, c.ob, c.o.inner_rtol);
             }
             c.ph.mark(kPhOuter, c.stream);
@@ -821,9 +840,9 @@ int amg_mass_apply(amg_ctx *ctx, int level, int which, const double *x, double *
         return dispatch_nb(c.nbp, [&](auto tag) {
             constexpr int NB = decltype(tag)::value;
             Solver<NB> S(c);
-            S.template elem<0>(n, OpPack<NB>{c.pk_in, x, nb}, NoFin{}, nullptr);
-            S.mass_apply(level, which, c.pk_in, c.pk_out, nullptr, nullptr);
-            S.template elem<0>(n, OpUnpack<NB>{y, c.pk_out, nb}, NoFin{}, nullptr);
+            const double *in = vec_in(S, n, x, c.pk_in, nb, y);
+            S.mass_apply(level, which, in, vec_out<NB>(y, c.pk_out, nb), nullptr, nullptr);
+            vec_done(S, n, y, c.pk_out, nb);
             AMG_HIP(hipStreamSynchronize(c.stream));
             return AMG_OK;
         });
@@ -839,8 +858,8 @@ int amg_mass_quad(amg_ctx *ctx, int which, const double *x, double *q_host, int 
         return dispatch_nb(c.nbp, [&](auto tag) {
             constexpr int NB = decltype(tag)::value;
             Solver<NB> S(c);
-            S.template elem<0>(n, OpPack<NB>{c.pk_in, x, nb}, NoFin{}, nullptr);
-            S.mass_apply(0, which, c.pk_in, c.pk_out, c.pk_in, c.dscratch);
+            const double *in = vec_in(S, n, x, c.pk_in, nb, nullptr);
+            S.mass_apply(0, which, in, c.pk_out, in, c.dscratch);
             AMG_HIP(hipMemcpyAsync(c.hscr, c.dscratch, 16 * sizeof(double), hipMemcpyDeviceToHost, c.stream));
             AMG_HIP(hipStreamSynchronize(c.stream));
             for (int k = 0; k < nb; ++k) q_host[k] = c.hscr[k];
