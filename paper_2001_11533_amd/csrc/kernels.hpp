@@ -1840,36 +1840,41 @@ template <> struct Vec16<float> {
     }
 };
 
-// One column with b of the matrix's type and 16-byte aligned: b is read in the
-// same 16-byte vectors as the matrix rows, eight vectors of each in flight per
-// lane (a float32 row of up to 2048 entries is one round).  Every load is
-// unconditional (guarded loads compile to a wait each): vectors past the row's
-// stride ld re-read its last vector, and entries past n are zeroed in both.  The
-// last vector of b may reach past its n entries, within the 256-byte granule
-// that every workspace vector is allocated in.  The stop flag is tested before
-// the store, so no load waits for it, and the few wavefronts per SIMD of such
-// a launch may use the registers that keep all loads in flight.
-template <typename TM>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) void dense_apply1_kernel(
+// At most four columns with b of the matrix's type and 16-byte aligned: b is
+// read in 16-byte vectors like the matrix rows, NB of them per vector of the
+// row, eight (four with four columns) row vectors and theirs in flight per lane
+// (a float32 row of up to 2048 entries is one round).  Every load is
+// unconditional (guarded loads compile to a wait each): vectors past the last
+// that holds an entry re-read it, and entries past n are zeroed in both.  The
+// last vector of b may reach past its entries, within the 16 bytes that hold
+// the last of them.  The stop flag is tested before the store, so no load waits
+// for it, and the few wavefronts per SIMD of such a launch may use the registers
+// that keep all loads in flight.
+template <typename TM, int NB>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) void dense_vec_kernel(
     const int *__restrict__ stop, int n, int ld, const TM *__restrict__ inv, const TM *__restrict__ b,
     TM *__restrict__ x) {
     using V = Vec16<TM>;
     using VT = typename V::type;
-    constexpr int W = V::n, D = 8;
+    constexpr int W = V::n, D = NB < 4 ? 8 : 4;
     const int lane = threadIdx.x % 64;
     const int i = (blockIdx.x * kBlock + threadIdx.x) / 64;
     if (i >= n) return;
     const int st = *stop;
-    const int last = (n - 1) / W * W;  // the vector that holds entry n - 1
-    double acc = 0.0;
+    const int last = (n - 1) / W * W;         // the vector that holds entry n - 1
+    const int lastb = (n * NB - 1) / W * W;  // and the last one of the batch
+    double acc[NB];
+#pragma unroll
+    for (int c = 0; c < NB; ++c) acc[c] = 0.0;
     const TM *row = inv + (size_t)i * ld;
     for (int k0 = lane * W; k0 < n; k0 += 64 * W * D) {
-        VT m[D], bv[D];
+        VT m[D], bv[D][NB];
 #pragma unroll
         for (int u = 0; u < D; ++u) {
             const int k = min(k0 + u * 64 * W, last);
             m[u] = *reinterpret_cast<const VT *>(row + k);
-            bv[u] = *reinterpret_cast<const VT *>(b + k);
+#pragma unroll
+            for (int q = 0; q < NB; ++q) bv[u][q] = *reinterpret_cast<const VT *>(b + min(k * NB + q * W, lastb));
         }
         // keep the scheduler from interleaving the loads with their uses
         // (it would otherwise issue them one at a time)
@@ -1879,11 +1884,23 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) 
 #pragma unroll
             for (int e = 0; e < W; ++e) {
                 const bool on = k0 + u * 64 * W + e < n;
-                acc += (on ? V::get(m[u], e) : 0.0) * (on ? V::get(bv[u], e) : 0.0);
+                const double a = on ? V::get(m[u], e) : 0.0;
+#pragma unroll
+                for (int c = 0; c < NB; ++c) {
+                    const int t = e * NB + c;
+                    acc[c] += a * (on ? V::get(bv[u][t / W], t % W) : 0.0);
+                }
             }
     }
-    acc = group_add<1>(acc, 64);
-    if (lane == 0 && !st) x[i] = (TM)acc;
+#pragma unroll
+    for (int c = 0; c < NB; ++c) acc[c] = group_add<1>(acc[c], 64);
+    if (lane < NB && !st) {
+        double v = acc[0];
+#pragma unroll
+        for (int c = 1; c < NB; ++c)
+            if (lane == c) v = acc[c];
+        x[(size_t)i * NB + lane] = (TM)v;
+    }
 }
 
 // Several columns: x = Inv B on the FP64 matrix cores.  A workgroup forms `rows`

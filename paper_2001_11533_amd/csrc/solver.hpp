@@ -182,13 +182,19 @@ template <int NB> struct Solver {
         const T *m;
         if constexpr (std::is_same_v<T, float>) m = d.m32;
         else m = d.m64;
-        // the vector kernel reads b (a workspace vector) in 16-byte vectors
-        if (NB == 1 && reinterpret_cast<uintptr_t>(b) % 16 == 0)
-            hipLaunchKernelGGL((dense_apply1_kernel<T>), dim3(ceil_div((long)d.n * 64, kBlock)), dim3(kBlock), 0, s,
-                               flag(stop), d.n, d.ld, m, b, x);
-        else
-            hipLaunchKernelGGL((dense_mm_kernel<T, NB>), dim3(ceil_div(d.n, dense_mm_rows(d.n))), dim3(64 * kMmWaves),
-                               0, s, flag(stop), d.n, d.ld, dense_mm_rows(d.n), m, b, x);
+        // up to four columns on the vector ALUs, whose wavefronts finish one by one
+        // without a reduction through LDS: a V-cycle of 10201 rows takes 38.4 (two
+        // columns) and 41.6 us (four), 42.5 and 43.5 with the matrix-core kernel,
+        // which is ahead from eight on (a lane's loads grow with the columns)
+        if constexpr (NB <= 4) {
+            if (reinterpret_cast<uintptr_t>(b) % 16 == 0) {
+                hipLaunchKernelGGL((dense_vec_kernel<T, NB>), dim3(ceil_div((long)d.n * 64, kBlock)), dim3(kBlock), 0,
+                                   s, flag(stop), d.n, d.ld, m, b, x);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((dense_mm_kernel<T, NB>), dim3(ceil_div(d.n, dense_mm_rows(d.n))), dim3(64 * kMmWaves), 0,
+                           s, flag(stop), d.n, d.ld, dense_mm_rows(d.n), m, b, x);
     }
 
     void read_sc(const CgScal *d) {
