@@ -265,9 +265,44 @@ __global__ void k_l1(int n, const int *rp, const double *v, double *dl1inv, doub
     }
 }
 
-__global__ void k_inv(int n, const double *d, double *dinv) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        dinv[i] = 1.0 / d[i];
+// Row sums and mass diagonal of a level in one pass: dl1inv (written unless
+// have_l1: coarsening a level forms it) with its float32 copy, mdinv = 1 / diag(M);
+// a non-positive diagonal entry of M sets *bad
+__global__ void k_level_diag(int n, const int *rp, const double *v, int have_l1, double *dl1inv, float *dl1inv32,
+                             const int *mrp, const int *mci, const double *mv, double *mdinv, int *bad) {
+    const int gl = row_lane();
+    for (int i = row_first(); i < n; i += row_stride()) {
+        double r = 0.0;
+        if (have_l1) {
+            r = dl1inv[i];
+        } else {
+            double s = 0.0;
+            const int e = rp[i + 1];
+            for (int p0 = rp[i]; p0 < e; p0 += kRowLanes) {
+                const int p = p0 + gl;
+                const double x = p < e ? fabs(v[p]) : 0.0;
+                const int cn = min(kRowLanes, e - p0);
+                for (int j = 0; j < cn; ++j) s = s + __shfl(x, j, kRowLanes);  // in the row's order
+            }
+            r = 1.0 / s;
+        }
+        double di = 0.0;
+        const int e = mrp[i + 1];
+        for (int p0 = mrp[i]; p0 < e; p0 += kRowLanes) {  // the last stored diagonal entry, as a serial loop
+            const int p = p0 + gl;
+            const bool hit = p < e && mci[p] == i;
+            const double x = hit ? mv[p] : 0.0;
+            const unsigned b = group_bits(hit);
+            const double y = __shfl(x, b ? 31 - __clz(b) : 0, kRowLanes);
+            if (b) di = y;
+        }
+        if (gl == 0) {
+            if (!have_l1) dl1inv[i] = r;
+            dl1inv32[i] = (float)r;
+            mdinv[i] = 1.0 / di;
+            if (!(di > 0.0)) atomicAdd(bad, 1);
+        }
+    }
 }
 
 __global__ void k_strength(int n, const int *rp, const int *ci, const double *v, const double *d,
@@ -1291,9 +1326,11 @@ __global__ __launch_bounds__(64 * NW) void k_spgemm_fill_dense(int n, int m, con
 }
 
 // out[p] = S[i, ci[p]] over row i of T (zero where S has no entry), both rows
-// sorted; a row of S with an entry outside T's row sets *bad
-__global__ void k_align(int n, const int *trp, const int *tci, const int *srp, const int *sci, const double *sv,
-                        double *out, int *bad) {
+// sorted; a row of S with an entry outside T's row sets *bad.  The float32
+// copies of out and of T's values and the 16-bit columns (when given) are
+// written in the same pass.
+__global__ void k_align(int n, const int *trp, const int *tci, const double *tv, const int *srp, const int *sci,
+                        const double *sv, double *out, float *out32, float *tv32, uint16_t *tc16, int *bad) {
     const int gl = row_lane();
     for (int i = row_first(); i < n; i += row_stride()) {
         const int qb = srp[i], qe = srp[i + 1];
@@ -1316,7 +1353,11 @@ __global__ void k_align(int n, const int *trp, const int *tci, const int *srp, c
                     else hi = mid - 1;
                 }
                 h = found >= 0;
-                out[p] = h ? sv[found] : 0.0;
+                const double x = h ? sv[found] : 0.0;
+                out[p] = x;
+                out32[p] = (float)x;
+                tv32[p] = (float)tv[p];
+                if (tc16) tc16[p] = (uint16_t)k;
             }
             hit += __popc(group_bits(h));
         }
@@ -1351,14 +1392,22 @@ __global__ __launch_bounds__(kBlock) void k_mirror(int n, const int *rp, const i
     }
 }
 
-__global__ void k_to_f32(long n, const double *a, float *b) {
-    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
-        b[i] = (float)a[i];
-}
-
-__global__ void k_to_u16(long n, const int *a, uint16_t *b) {
-    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
-        b[i] = (uint16_t)a[i];
+// float32 copies of several arrays in one launch (the hierarchy's copies are
+// some thirty arrays, most of them shorter than a launch is long)
+constexpr int kCopies = 16;
+struct Copies {
+    int n = 0;
+    long len[kCopies];
+    const double *src[kCopies];
+    float *dst[kCopies];
+};
+__global__ void k_to_f32(Copies cp) {
+    for (int a = 0; a < cp.n; ++a) {
+        const double *src = cp.src[a];
+        float *dst = cp.dst[a];
+        for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < cp.len[a]; i += (long)gridDim.x * blockDim.x)
+            dst[i] = (float)src[i];
+    }
 }
 
 // ---- dense kernels (coarsest level) ----
@@ -1677,18 +1726,44 @@ __global__ void k_sell_width(int n, int nsl, const int *rp, const int *ci, int *
     }
 }
 
-__global__ void k_sell_fill(int n, int nsl, const int *rp, const int *ci, const double *v, const int *soff,
-                            const int *base, uint16_t *scd, double *sv) {
-    const int lane = threadIdx.x % 64;
+// The slice's entries are contiguous in the CSR arrays: a slice of at most
+// kSellStage of them is read in order into LDS (a lane reading its own row
+// strides through memory by the row length) and written from there, with the
+// float32 values when sv32 is given.  Bound by memory: 274625 rows of 15
+// entries 98 + 5 us (values, then float32) before, 43 us now.
+constexpr int kSellStage = 1024;
+__global__ __launch_bounds__(kBlock) void k_sell_fill(int n, int nsl, const int *rp, const int *ci, const double *v,
+                                                      const int *soff, const int *base, uint16_t *scd, double *sv,
+                                                      float *sv32) {
+    __shared__ double lv[kBlock / 64][kSellStage];
+    __shared__ uint16_t lc[kBlock / 64][kSellStage];
+    const int lane = threadIdx.x % 64, wv = threadIdx.x / 64;
     const int w = (blockIdx.x * blockDim.x + threadIdx.x) / 64, nw = gridDim.x * blockDim.x / 64;
     for (int sl = w; sl < nsl; sl += nw) {
         const int r = sl * 64 + lane;
         const int o = soff[sl], wd = (soff[sl + 1] - o) / 64, b = base[sl];
-        const int p0 = r < n ? rp[r] : 0, len = r < n ? rp[r + 1] - p0 : 0;
+        const int p0 = rp[min(r, n)], len = rp[min(r + 1, n)] - p0;
+        const int first = __shfl(p0, 0), cnt = __shfl(p0 + len, 63) - first;
+        const bool staged = cnt <= kSellStage;
+        if (staged) {
+            wave_sync();  // the reads of the slice before
+            for (int e = lane; e < cnt; e += 64) {
+                lc[wv][e] = (uint16_t)(ci[first + e] - b);
+                lv[wv][e] = v[first + e];
+            }
+            wave_sync();
+        }
         for (int k = 0; k < wd; ++k) {
             const size_t q = (size_t)o + (size_t)k * 64 + lane;
-            scd[q] = (uint16_t)(k < len ? ci[p0 + k] - b : 0);
-            sv[q] = k < len ? v[p0 + k] : 0.0;
+            uint16_t cd = 0;
+            double x = 0.0;
+            if (k < len) {
+                cd = staged ? lc[wv][p0 - first + k] : (uint16_t)(ci[p0 + k] - b);
+                x = staged ? lv[wv][p0 - first + k] : v[p0 + k];
+            }
+            scd[q] = cd;
+            sv[q] = x;
+            if (sv32) sv32[q] = (float)x;
         }
     }
 }
@@ -1901,13 +1976,14 @@ struct Setup {
         if (f[kFlagFill]) fail(AMG_ERR_CAPACITY, "sparse product: output column lost in the fill");
     }
 
-    // out[0..n] exclusive scan of cnt[0..n-1]; the total is left in isc[8]
-    // and returned when read (else -1: no wait for the device)
-    int scan(const int *cnt, int *out, int n, bool read = true) {
+    // out[0..n] exclusive scan of cnt[0..n-1]; the total is left in isc[8] and
+    // returned when read (else -1: no wait for the device), or left in *tot
+    int scan(const int *cnt, int *out, int n, bool read = true, int *tot = nullptr) {
         const int nb = std::max(1, ceil_div(n, kScanPer));
         int *bsum = c.arena.alloc<int>(nb);
         if (n > 0) hipLaunchKernelGGL(k_scan_blocks, dim3(nb), dim3(kBlock), 0, s, n, cnt, bsum);
-        hipLaunchKernelGGL(k_scan_final, dim3(nb), dim3(kBlock), 0, s, n, nb, cnt, bsum, out, isc + 8);
+        hipLaunchKernelGGL(k_scan_final, dim3(nb), dim3(kBlock), 0, s, n, nb, cnt, bsum, out,
+                           tot ? tot : isc + 8);
         const int total = read ? read_int(isc + 8) : -1;
         rel(bsum);
         return total;
@@ -2320,51 +2396,69 @@ struct Setup {
         const int n = L.A.n;
         L.n = n;
         if (!L.dl1inv) L.dl1inv = c.arena.alloc<double>(n);
-        double *dl1 = c.arena.alloc<double>(n);
-        hipLaunchKernelGGL(k_l1, dim3(gsz((long)(n) * kRowLanes)), dim3(kBlock), 0, s, n, L.A.rp, L.A.v, L.dl1inv, dl1);
-        double *md = c.arena.alloc<double>(n);
+        L.dl1inv32 = c.arena.alloc<float>(n);
         L.mdinv = c.arena.alloc<double>(n);
-        hipLaunchKernelGGL(k_diag, dim3(gsz((long)(n) * kRowLanes)), dim3(kBlock), 0, s, n, L.M.rp, L.M.ci, L.M.v,
-                           (const uint8_t *)nullptr, md, c.iscratch + kFlagMassDiag);
-        hipLaunchKernelGGL(k_inv, dim3(gsz(n)), dim3(kBlock), 0, s, n, md, L.mdinv);
+        hipLaunchKernelGGL(k_level_diag, dim3(gsz((long)(n) * kRowLanes)), dim3(kBlock), 0, s, n, L.A.rp, L.A.v,
+                           L.S.v ? 1 : 0, L.dl1inv, L.dl1inv32, L.M.rp, L.M.ci, L.M.v, L.mdinv,
+                           c.iscratch + kFlagMassDiag);
         check_kernels();
-        c.arena.release(dl1);
-        c.arena.release(md);
     }
 
-    void make_sell(DCsr &A) {
-        const int nsl = ceil_div(A.n, 64);
-        int *cnt = c.arena.alloc<int>(nsl + 1);
-        int *off = c.arena.alloc<int>(nsl + 1);
-        int *base = c.arena.alloc<int>(nsl);
-        zero(isc + 13, 2 * sizeof(int));
-        hipLaunchKernelGGL(k_sell_width, dim3(gwave(nsl)), dim3(kBlock), 0, s, A.n, nsl, A.rp, A.ci, cnt, base,
-                           isc + 13, isc + 14);
-        scan(cnt, off, nsl, false);
-        // the total (isc[8]) and the flags of a wide slice (isc[13]) and of a
-        // slice wider than 8 entries (isc[14]) in one read
-        AMG_HIP(hipMemcpyAsync(hisc + 8, isc + 8, 7 * sizeof(int), hipMemcpyDeviceToHost, s));
+    // the float32 copies queued so far, in one launch
+    Copies copies;
+    void f32(const double *src, float *dst, long len) {
+        if (len == 0) return;
+        copies.src[copies.n] = src;
+        copies.dst[copies.n] = dst;
+        copies.len[copies.n] = len;
+        if (++copies.n == kCopies) f32_run();
+    }
+    void f32_run() {
+        long most = 0;
+        for (int a = 0; a < copies.n; ++a) most = std::max(most, copies.len[a]);
+        if (copies.n) hipLaunchKernelGGL(k_to_f32, dim3(gsz(most)), dim3(kBlock), 0, s, copies);
+        copies.n = 0;
+    }
+
+    // sliced-ELL copies of two matrices: their widths are counted before the
+    // one wait for both totals
+    static constexpr int kSellWord = 48, kSellWords = 4;  // per matrix: total, wide, over8
+    void make_sell(DCsr &A0, DCsr &A1) {
+        DCsr *mat[2] = {&A0, &A1};
+        int *cnt[2];
+        zero(isc + kSellWord, 2 * kSellWords * sizeof(int));
+        for (int q = 0; q < 2; ++q) {
+            DCsr &A = *mat[q];
+            int *w = isc + kSellWord + q * kSellWords;
+            A.nsl = ceil_div(A.n, 64);
+            cnt[q] = c.arena.alloc<int>(A.nsl + 1);
+            A.sl_off = c.arena.alloc<int>(A.nsl + 1);
+            A.sl_base = c.arena.alloc<int>(A.nsl);
+            hipLaunchKernelGGL(k_sell_width, dim3(gwave(A.nsl)), dim3(kBlock), 0, s, A.n, A.nsl, A.rp, A.ci, cnt[q],
+                               A.sl_base, w + 1, w + 2);
+            scan(cnt[q], A.sl_off, A.nsl, false, w);
+        }
+        AMG_HIP(hipMemcpyAsync(hisc, isc + kSellWord, 2 * kSellWords * sizeof(int), hipMemcpyDeviceToHost, s));
         AMG_HIP(hipStreamSynchronize(s));
-        const int tot = hisc[8];
-        c.arena.release(cnt);
-        if (hisc[13]) {  // 16-bit column offsets do not reach: the CSR kernels serve this matrix
-            c.arena.release(off);
-            c.arena.release(base);
-            return;
+        for (int q = 0; q < 2; ++q) {
+            DCsr &A = *mat[q];
+            const int tot = hisc[q * kSellWords];
+            c.arena.release(cnt[q]);
+            if (hisc[q * kSellWords + 1]) {  // 16-bit column offsets do not reach: the CSR kernels serve this matrix
+                c.arena.release(A.sl_off);
+                c.arena.release(A.sl_base);
+                A.sl_off = A.sl_base = nullptr;
+                A.nsl = 0;
+                continue;
+            }
+            A.sl_over8 = hisc[q * kSellWords + 2] != 0;
+            A.sl_cd = c.arena.alloc<uint16_t>(tot);
+            A.sl_v = c.arena.alloc<double>(tot);
+            if (A.v32) A.sl_v32 = c.arena.alloc<float>(tot);
+            A.sl_tot = tot;
+            hipLaunchKernelGGL(k_sell_fill, dim3(gwave(A.nsl)), dim3(kBlock), 0, s, A.n, A.nsl, A.rp, A.ci, A.v,
+                               A.sl_off, A.sl_base, A.sl_cd, A.sl_v, A.sl_v32);
         }
-        A.sl_off = off;
-        A.sl_base = base;
-        A.sl_over8 = hisc[14] != 0;
-        A.sl_cd = c.arena.alloc<uint16_t>(tot);
-        A.sl_v = c.arena.alloc<double>(tot);
-        hipLaunchKernelGGL(k_sell_fill, dim3(gwave(nsl)), dim3(kBlock), 0, s, A.n, nsl, A.rp, A.ci, A.v, A.sl_off,
-                           A.sl_base, A.sl_cd, A.sl_v);
-        if (A.v32) {
-            A.sl_v32 = c.arena.alloc<float>(tot);
-            hipLaunchKernelGGL(k_to_f32, dim3(gsz(tot)), dim3(kBlock), 0, s, (long)tot, A.sl_v, A.sl_v32);
-        }
-        A.nsl = nsl;
-        A.sl_tot = tot;
         check_kernels();
     }
 
@@ -2540,7 +2634,7 @@ void build_hierarchy(Ctx &c, const amg_csr &Ain, const amg_csr &Min, const uint8
     auto f32 = [&](DCsr &m) {
         if (!m.v || m.nnz == 0) return;
         m.v32 = c.arena.alloc<float>(m.nnz);
-        hipLaunchKernelGGL(k_to_f32, dim3(gsz(m.nnz)), dim3(kBlock), 0, s, (long)m.nnz, m.v, m.v32);
+        su.f32(m.v, m.v32, m.nnz);
     };
     for (auto &L : c.lev) {
         f32(L.A);
@@ -2552,23 +2646,19 @@ void build_hierarchy(Ctx &c, const amg_csr &Ain, const amg_csr &Min, const uint8
             // S's values on the pattern of T = A S, for the fused coarse
             // correction (after the level loop: off the path to the side stream)
             L.Ts = c.arena.alloc<double>(L.T.nnz);
-            hipLaunchKernelGGL(k_align, dim3(gsz((long)(L.n) * kRowLanes)), dim3(kBlock), 0, s, L.n, L.T.rp, L.T.ci, L.S.rp, L.S.ci,
-                               L.S.v, L.Ts, c.iscratch + Setup::kFlagAlign);
-            f32(L.T);
             L.Ts32 = c.arena.alloc<float>(L.T.nnz);
-            hipLaunchKernelGGL(k_to_f32, dim3(gsz(L.T.nnz)), dim3(kBlock), 0, s, (long)L.T.nnz, L.Ts, L.Ts32);
-            if (L.T.m <= 65536 && L.T.nnz > 0) {  // T's columns are coarse indices: 16 bits suffice
-                L.Tc16 = c.arena.alloc<uint16_t>(L.T.nnz);
-                hipLaunchKernelGGL(k_to_u16, dim3(gsz(L.T.nnz)), dim3(kBlock), 0, s, (long)L.T.nnz, L.T.ci, L.Tc16);
-            }
+            if (L.T.nnz > 0) L.T.v32 = c.arena.alloc<float>(L.T.nnz);
+            // T's columns are coarse indices: 16 bits suffice
+            if (L.T.m <= 65536 && L.T.nnz > 0) L.Tc16 = c.arena.alloc<uint16_t>(L.T.nnz);
+            hipLaunchKernelGGL(k_align, dim3(gsz((long)(L.n) * kRowLanes)), dim3(kBlock), 0, s, L.n, L.T.rp, L.T.ci,
+                               L.T.v, L.S.rp, L.S.ci, L.S.v, L.Ts, L.Ts32, L.T.v32, L.Tc16,
+                               c.iscratch + Setup::kFlagAlign);
         }
-        L.dl1inv32 = c.arena.alloc<float>(L.n);
-        hipLaunchKernelGGL(k_to_f32, dim3(gsz(L.n)), dim3(kBlock), 0, s, (long)L.n, L.dl1inv, L.dl1inv32);
     }
+    su.f32_run();
     // sliced-ELL copies of the finest-level A and M (rows of near-equal length;
     // the prolongator's rows vary too much for the padding to pay)
-    su.make_sell(c.lev[0].A);
-    su.make_sell(c.lev[0].M);
+    su.make_sell(c.lev[0].A, c.lev[0].M);
     su.check_kernels();
     // dense inverse of the coarsest stiffness matrix
     Level &Lc = c.lev[c.L - 1];
