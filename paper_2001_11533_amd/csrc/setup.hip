@@ -387,51 +387,88 @@ __global__ void k_mis_init(int n, const uint8_t *mask, int8_t *st) {
 // issued in batches ahead of the one read that ends the loop.
 __device__ __forceinline__ bool mis_done(const int *prev) { return prev && *prev == 0; }
 
+// The rounds and the aggregation passes take G lanes per row: one where rows are
+// short (a row is then one or two loads' latency), kRowLanes where they are long,
+// the small coarse levels with rows of up to a hundred strong neighbours, whose
+// serial walk was the length of the launch (1648 rows: 25 us for each of the first
+// passes, now 4).  The lanes' results are combined by the same total order, so
+// the roots and aggregates do not depend on G.
+template <int G> __device__ __forceinline__ int grp_lane() { return threadIdx.x % G; }
+template <int G> __device__ __forceinline__ int grp_row() {
+    return (int)((blockIdx.x * blockDim.x + threadIdx.x) / G);
+}
+template <int G> __device__ __forceinline__ int grp_stride() { return (int)(gridDim.x * blockDim.x / G); }
+template <int G> __device__ __forceinline__ int prio_max(const uint64_t *h, int best) {
+    for (int off = G / 2; off > 0; off >>= 1) {
+        const int o = __shfl_xor(best, off);
+        if (prio_gt(h, o, best)) best = o;
+    }
+    return best;
+}
+template <int G> __device__ __forceinline__ bool grp_any(bool x) {
+    if constexpr (G == 1) return x;
+    else return group_bits(x) != 0;
+}
+static_assert(kRowLanes == 16, "group_bits");
+
+template <int G>
 __global__ void k_mis_m1(int n, const int *srp, const int *sci, const uint64_t *h, const int8_t *st,
                          int *m1, const int *prev) {
     if (mis_done(prev)) return;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    for (int i = grp_row<G>(); i < n; i += grp_stride<G>()) {
         int best = st[i] == UNDEC ? i : -1;
-        for (int p = srp[i]; p < srp[i + 1]; ++p) {
+        const int e = srp[i + 1];
+        for (int p = srp[i] + grp_lane<G>(); p < e; p += G) {
             const int k = sci[p];
             if (st[k] == UNDEC && prio_gt(h, k, best)) best = k;
         }
-        m1[i] = best;
+        best = prio_max<G>(h, best);
+        if (grp_lane<G>() == 0) m1[i] = best;
     }
 }
 
+template <int G>
 __global__ void k_mis_m2(int n, const int *srp, const int *sci, const uint64_t *h, const int *m1,
                          int8_t *st, const int *prev) {
     if (mis_done(prev)) return;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    for (int i = grp_row<G>(); i < n; i += grp_stride<G>()) {
         if (st[i] != UNDEC) continue;
         int best = m1[i];
-        for (int p = srp[i]; p < srp[i + 1]; ++p) {
+        const int e = srp[i + 1];
+        for (int p = srp[i] + grp_lane<G>(); p < e; p += G) {
             const int k = m1[sci[p]];
             if (prio_gt(h, k, best)) best = k;
         }
-        if (best == i) st[i] = ROOT;
+        best = prio_max<G>(h, best);
+        if (grp_lane<G>() == 0 && best == i) st[i] = ROOT;
     }
 }
 
+template <int G>
 __global__ void k_mis_r1(int n, const int *srp, const int *sci, const int8_t *st, uint8_t *r1,
                          const int *prev) {
     if (mis_done(prev)) return;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        uint8_t any = st[i] == ROOT;
-        for (int p = srp[i]; p < srp[i + 1] && !any; ++p) any = st[sci[p]] == ROOT;
-        r1[i] = any;
+    for (int i = grp_row<G>(); i < n; i += grp_stride<G>()) {
+        bool any = st[i] == ROOT;
+        const int e = srp[i + 1];
+        for (int p = srp[i] + grp_lane<G>(); p < e && !any; p += G) any = st[sci[p]] == ROOT;
+        any = grp_any<G>(any);
+        if (grp_lane<G>() == 0) r1[i] = any;
     }
 }
 
+template <int G>
 __global__ void k_mis_r2(int n, const int *srp, const int *sci, const uint8_t *r1, int8_t *st, int *undec,
                          const int *prev) {
     if (mis_done(prev)) return;
     int left = 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    for (int i = grp_row<G>(); i < n; i += grp_stride<G>()) {
         if (st[i] != UNDEC) continue;
         bool any = r1[i];
-        for (int p = srp[i]; p < srp[i + 1] && !any; ++p) any = r1[sci[p]];
+        const int e = srp[i + 1];
+        for (int p = srp[i] + grp_lane<G>(); p < e && !any; p += G) any = r1[sci[p]];
+        any = grp_any<G>(any);
+        if (grp_lane<G>() != 0) continue;
         if (any) st[i] = OUT;
         else ++left;
     }
@@ -456,61 +493,73 @@ __global__ void k_root_flags(int n, const int8_t *st, uint8_t *root, int *cnt) {
     }
 }
 
+// the entry of row i with the largest sabs among those with sel[column], the
+// smallest column of equal ones, and its column (-1: none); G lanes per row
+template <int G>
+__device__ __forceinline__ int strongest(int i, const int *srp, const int *sci, const double *sabs,
+                                         const uint8_t *sel) {
+    int bk = -1;
+    double ba = 0.0;
+    const int e = srp[i + 1];
+    for (int p = srp[i] + grp_lane<G>(); p < e; p += G) {
+        const int k = sci[p];
+        if (!sel[k]) continue;
+        const double a = sabs[p];
+        if (bk < 0 || a > ba) {  // ascending k: ties keep the smaller k
+            bk = k;
+            ba = a;
+        }
+    }
+    for (int off = G / 2; off > 0; off >>= 1) {
+        const int ok = __shfl_xor(bk, off);
+        const double oa = __shfl_xor(ba, off);
+        if (ok >= 0 && (bk < 0 || oa > ba || (oa == ba && ok < bk))) {
+            bk = ok;
+            ba = oa;
+        }
+    }
+    return bk;
+}
+
 // phase 2: roots get their coarse id, nodes next to a root join the strongest root
+template <int G>
 __global__ void k_phase2(int n, const int *srp, const int *sci, const double *sabs, const uint8_t *root,
                          const int *cid, const uint8_t *mask, int *agg, uint8_t *p2) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        p2[i] = 0;
-        if (mask && mask[i]) {
-            agg[i] = -1;
-            continue;
-        }
-        if (root[i]) {
-            agg[i] = cid[i];
-            continue;
-        }
-        int bk = -1;
-        double ba = 0.0;
-        for (int p = srp[i]; p < srp[i + 1]; ++p) {
-            const int k = sci[p];
-            if (!root[k]) continue;
-            const double a = sabs[p];
-            if (bk < 0 || a > ba) {  // ascending k: ties keep the smaller k
-                bk = k;
-                ba = a;
+    for (int i = grp_row<G>(); i < n; i += grp_stride<G>()) {
+        int a = -1;
+        bool near = false;
+        if (!(mask && mask[i])) {
+            if (root[i]) {
+                a = cid[i];
+            } else {
+                const int bk = strongest<G>(i, srp, sci, sabs, root);
+                near = bk >= 0;
+                a = near ? cid[bk] : -2;
             }
         }
-        if (bk >= 0) {
-            agg[i] = cid[bk];
-            p2[i] = 1;
-        } else {
-            agg[i] = -2;
+        if (grp_lane<G>() == 0) {
+            agg[i] = a;
+            p2[i] = near;
         }
     }
 }
 
+template <int G>
 __global__ void k_phase3(int n, const int *srp, const int *sci, const double *sabs, const uint8_t *p2,
                          int *agg, int *unassigned) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    for (int i = grp_row<G>(); i < n; i += grp_stride<G>()) {
         if (agg[i] != -2) continue;
-        int bk = -1;
-        double ba = 0.0;
-        for (int p = srp[i]; p < srp[i + 1]; ++p) {
-            const int k = sci[p];
-            if (!p2[k]) continue;
-            const double a = sabs[p];
-            if (bk < 0 || a > ba) {
-                bk = k;
-                ba = a;
-            }
-        }
+        const int bk = strongest<G>(i, srp, sci, sabs, p2);
+        if (grp_lane<G>() != 0) continue;
         if (bk >= 0) agg[i] = agg[bk];
         else atomicAdd(unassigned, 1);
     }
 }
 
-__global__ void k_rho(int n, const double *dl1, const double *d, const uint8_t *mask,
-                      unsigned long long *maxbits) {
+// max_i dl1[i] / d[i]: one update per workgroup (its wavefronts' updates of the
+// one word queue up: 274625 rows 43 us with one each, now 17 us)
+__global__ __launch_bounds__(kBlock) void k_rho(int n, const double *dl1, const double *d, const uint8_t *mask,
+                                                unsigned long long *maxbits) {
     // r > 0: the order of the bit patterns is the order of the values
     unsigned long long m = 0;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
@@ -519,7 +568,12 @@ __global__ void k_rho(int n, const double *dl1, const double *d, const uint8_t *
         m = max(m, (unsigned long long)__double_as_longlong(r));
     }
     for (int off = 32; off > 0; off >>= 1) m = max(m, (unsigned long long)__shfl_xor(m, off));
-    if (threadIdx.x % 64 == 0 && m) raise_max(maxbits, m);
+    __shared__ unsigned long long wm[kBlock / 64];
+    if (threadIdx.x % 64 == 0) wm[threadIdx.x / 64] = m;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < kBlock / 64; ++w) m = max(m, wm[w]);
+    if (m) raise_max(maxbits, m);
 }
 
 // tentative prolongator: one unit entry per non-Dirichlet row
@@ -2315,26 +2369,34 @@ struct Setup {
         int *m1 = c.arena.alloc<int>(n);
         uint8_t *r1 = c.arena.alloc<uint8_t>(n);
         hipLaunchKernelGGL(k_mis_init, dim3(gsz(n)), dim3(kBlock), 0, s, n, mask, st);
-        // rounds in batches with one read of the undecided flag per batch;
-        // round r leaves a nonzero und[r % kMisRing] while nodes are undecided
-        // (the ring holds whole batches)
-        constexpr int kMisRing = 64, kMisBatch = 4;
+        // rounds in batches with one read of the undecided flag per batch (most
+        // levels take five to eight rounds; a round past the last returns at
+        // once); round r leaves a nonzero und[r % kMisRing] while nodes are
+        // undecided (the ring holds whole batches)
+        constexpr int kMisRing = 64, kMisBatch = 8;
         static_assert(kMisRing % kMisBatch == 0, "a batch must not wrap the ring");
         int *und = c.arena.alloc<int>(kMisRing);
-        for (int round = 0;;) {
-            if (round > n + 1) fail(AMG_ERR_ARG, "independent-set rounds did not terminate");
-            zero(und + round % kMisRing, kMisBatch * sizeof(int));
-            for (int b = 0; b < kMisBatch; ++b, ++round) {
-                const int *prev = round ? und + (round - 1) % kMisRing : nullptr;
-                hipLaunchKernelGGL(k_mis_m1, dim3(gsz(n)), dim3(kBlock), 0, s, n, srp, sci, h, st, m1, prev);
-                hipLaunchKernelGGL(k_mis_m2, dim3(gsz(n)), dim3(kBlock), 0, s, n, srp, sci, h, m1, st, prev);
-                hipLaunchKernelGGL(k_mis_r1, dim3(gsz(n)), dim3(kBlock), 0, s, n, srp, sci, st, r1, prev);
-                hipLaunchKernelGGL(k_mis_r2, dim3(gsz(n)), dim3(kBlock), 0, s, n, srp, sci, r1, st,
-                                   und + round % kMisRing, prev);
+        auto rounds = [&](auto tag) {
+            constexpr int G = decltype(tag)::value;
+            const dim3 g(gsz((long)n * G));
+            for (int round = 0;;) {
+                if (round > n + 1) fail(AMG_ERR_ARG, "independent-set rounds did not terminate");
+                zero(und + round % kMisRing, kMisBatch * sizeof(int));
+                for (int b = 0; b < kMisBatch; ++b, ++round) {
+                    const int *prev = round ? und + (round - 1) % kMisRing : nullptr;
+                    hipLaunchKernelGGL(k_mis_m1<G>, g, dim3(kBlock), 0, s, n, srp, sci, h, st, m1, prev);
+                    hipLaunchKernelGGL(k_mis_m2<G>, g, dim3(kBlock), 0, s, n, srp, sci, h, m1, st, prev);
+                    hipLaunchKernelGGL(k_mis_r1<G>, g, dim3(kBlock), 0, s, n, srp, sci, st, r1, prev);
+                    hipLaunchKernelGGL(k_mis_r2<G>, g, dim3(kBlock), 0, s, n, srp, sci, r1, st,
+                                       und + round % kMisRing, prev);
+                }
+                check_kernels();
+                if (read_int(und + (round - 1) % kMisRing) == 0) break;
             }
-            check_kernels();
-            if (read_int(und + (round - 1) % kMisRing) == 0) break;
-        }
+        };
+        const bool long_rows = A.nnz > 16L * n;
+        if (long_rows) rounds(std::integral_constant<int, kRowLanes>{});
+        else rounds(std::integral_constant<int, 1>{});
         c.arena.release(und);
         L0.root = c.arena.alloc<uint8_t>(n);
         int *cid = c.arena.alloc<int>(n + 1);
@@ -2342,10 +2404,15 @@ struct Setup {
         scan(cnt, cid, n, false);  // the aggregate count stays in isc[8], read with the check below
         L0.agg = c.arena.alloc<int>(n);
         uint8_t *p2 = c.arena.alloc<uint8_t>(n);
-        hipLaunchKernelGGL(k_phase2, dim3(gsz(n)), dim3(kBlock), 0, s, n, srp, sci, sabs, L0.root, cid, mask,
-                           L0.agg, p2);
         zero(isc + 7, sizeof(int));
-        hipLaunchKernelGGL(k_phase3, dim3(gsz(n)), dim3(kBlock), 0, s, n, srp, sci, sabs, p2, L0.agg, isc + 7);
+        auto join = [&](auto tag) {
+            constexpr int G = decltype(tag)::value;
+            const dim3 g(gsz((long)n * G));
+            hipLaunchKernelGGL(k_phase2<G>, g, dim3(kBlock), 0, s, n, srp, sci, sabs, L0.root, cid, mask, L0.agg, p2);
+            hipLaunchKernelGGL(k_phase3<G>, g, dim3(kBlock), 0, s, n, srp, sci, sabs, p2, L0.agg, isc + 7);
+        };
+        if (long_rows) join(std::integral_constant<int, kRowLanes>{});
+        else join(std::integral_constant<int, 1>{});
         check_kernels();
         AMG_HIP(hipMemcpyAsync(hisc + 7, isc + 7, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
         AMG_HIP(hipStreamSynchronize(s));
