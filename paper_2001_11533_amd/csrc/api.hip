@@ -577,11 +577,23 @@ int amg_setup(const amg_csr *A, const amg_csr *M, const uint8_t *dirichlet, cons
         c.iscratch2 = c.arena.alloc<int>(64);
         c.never = c.arena.alloc<int>(1);
         AMG_HIP(hipMemsetAsync(c.never, 0, sizeof(int), c.stream));
-        AMG_HIP(hipHostMalloc((void **)&c.hsc, sizeof(CgScal), hipHostMallocDefault));
-        AMG_HIP(hipHostMalloc((void **)&c.hscr, 64 * sizeof(double), hipHostMallocDefault));
-        AMG_HIP(hipHostMalloc((void **)&c.hiscr, 64 * sizeof(int), hipHostMallocDefault));
-        AMG_HIP(hipHostMalloc((void **)&c.hiscr2, 64 * sizeof(int), hipHostMallocDefault));
-        AMG_HIP(hipHostMalloc((void **)&c.mails, 64 * sizeof(Mail), hipHostMallocDefault));
+        // one pinned block (an allocation takes tens of microseconds), a cache
+        // line apart from each other
+        size_t pin = 0;
+        auto carve = [&](auto *&p, size_t n) {
+            using P = std::remove_reference_t<decltype(*p)>;
+            if (c.pinned) p = reinterpret_cast<P *>(c.pinned + pin);
+            pin += (n * sizeof(P) + 127) / 128 * 128;
+        };
+        for (int pass = 0; pass < 2; ++pass) {  // the size, then the parts
+            pin = 0;
+            carve(c.hsc, 1);
+            carve(c.hscr, 64);
+            carve(c.hiscr, 64);
+            carve(c.hiscr2, 64);
+            carve(c.mails, 64);
+            if (!c.pinned) AMG_HIP(hipHostMalloc((void **)&c.pinned, pin, hipHostMallocDefault));
+        }
         AMG_HIP(hipStreamCreateWithFlags(&c.cap_stream, hipStreamNonBlocking));
         AMG_HIP(hipStreamCreateWithFlags(&c.side, hipStreamNonBlocking));
         AMG_HIP(hipStreamCreateWithFlags(&c.gal, hipStreamNonBlocking));
@@ -612,11 +624,7 @@ int amg_destroy(amg_ctx *ctx) {
     if (c.side) (void)hipStreamSynchronize(c.side);  // setup that failed before joining it
     if (c.gal) (void)hipStreamSynchronize(c.gal);
     c.arena.free_all();
-    if (c.hsc) (void)hipHostFree(c.hsc);
-    if (c.hscr) (void)hipHostFree(c.hscr);
-    if (c.hiscr) (void)hipHostFree(c.hiscr);
-    if (c.hiscr2) (void)hipHostFree(c.hiscr2);
-    if (c.mails) (void)hipHostFree(c.mails);
+    if (c.pinned) (void)hipHostFree(c.pinned);
     for (auto g : c.graphs) (void)hipGraphExecDestroy(g);
     for (auto e : c.poll_ev)
         if (e) (void)hipEventDestroy(e);

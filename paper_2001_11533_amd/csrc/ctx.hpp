@@ -157,6 +157,7 @@ struct Ctx {
     double *part[3] = {nullptr, nullptr, nullptr};  // reduction partials [2*16*kMaxGrid] each
     int pgrid[3] = {0, 0, 0};                       // workgroups that wrote each buffer
     double *dscratch = nullptr;  // small device scalars [64]
+    char *pinned = nullptr;      // the pinned block that holds the host words below
     int *iscratch = nullptr;     // small device ints [64]
     int *never = nullptr;        // a stop flag that stays zero (kernels launched without one)
     // host mirrors

@@ -1856,13 +1856,13 @@ __global__ void k_gemm(int n, const double *A, int transA, const double *B, doub
 }
 
 // H = 1/2 (T + T^T), T = XtY + beta Mu
-__global__ void k_hsym(int n, const double *XtY, const double *Mu, double beta, double *H) {
+__global__ void k_hsym(int n, const double *XtY, const double *Mu, double beta, double *H, double *Hf) {
     const long tot = (long)n * n;
     for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < tot; e += (long)gridDim.x * blockDim.x) {
         const int i = (int)(e / n), j = (int)(e % n);
         const double tij = XtY[(size_t)i * n + j] + beta * Mu[(size_t)i * n + j];
         const double tji = XtY[(size_t)j * n + i] + beta * Mu[(size_t)j * n + i];
-        H[e] = 0.5 * (tij + tji);
+        H[e] = Hf[e] = 0.5 * (tij + tji);
     }
 }
 
@@ -2059,14 +2059,24 @@ struct Setup {
         return d;
     }
 
-    void check_matrix(const DCsr &d, const char *name) {
-        zero(c.iscratch, 2 * sizeof(int));
-        hipLaunchKernelGGL(k_check_sym, dim3(gsz((long)(d.n) * kRowLanes)), dim3(kBlock), 0, s, d.n, d.rp, d.ci, d.v, c.iscratch);
+    // both input matrices, with one wait
+    void check_matrices(const DCsr &A, const DCsr &M) {
+        zero(c.iscratch, 4 * sizeof(int));
+        int *bad = c.iscratch;
+        for (const DCsr *d : {&A, &M}) {
+            hipLaunchKernelGGL(k_check_sym, dim3(gsz((long)(d->n) * kRowLanes)), dim3(kBlock), 0, s, d->n, d->rp,
+                               d->ci, d->v, bad);
+            bad += 2;
+        }
         check_kernels();
-        AMG_HIP(hipMemcpyAsync(c.hiscr, c.iscratch, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+        AMG_HIP(hipMemcpyAsync(c.hiscr, c.iscratch, 4 * sizeof(int), hipMemcpyDeviceToHost, s));
         AMG_HIP(hipStreamSynchronize(s));
-        if (c.hiscr[1]) fail(AMG_ERR_ARG, std::string(name) + ": columns not sorted/unique within a row");
-        if (c.hiscr[0]) fail(AMG_ERR_NOT_SYMMETRIC, std::string(name) + " is not exactly symmetric");
+        const int *f = c.hiscr;
+        for (const char *name : {"A", "M"}) {
+            if (f[1]) fail(AMG_ERR_ARG, std::string(name) + ": columns not sorted/unique within a row");
+            if (f[0]) fail(AMG_ERR_NOT_SYMMETRIC, std::string(name) + " is not exactly symmetric");
+            f += 2;
+        }
     }
 
     // A sparse product in three phases so that two can run on two streams with
@@ -2093,8 +2103,7 @@ struct Setup {
         pr.cnt = c.arena.alloc<int>(A.n + 1);
         C.rp = c.arena.alloc<int>(A.n + 1);
         int *cnt = pr.cnt;
-        zero(isc + 4, sizeof(int));
-        zero(isc + 10, 3 * sizeof(int));
+        zero(isc + 4, 12 * sizeof(int));  // one 16-byte aligned fill over all result words
         // rows too few to fill the chip: four wavefronts per row; otherwise
         // groups of 16, 32 or 64 lanes per row, from the mean row length of A
         const bool wide = pr.wide = A.n < 8192;
@@ -2275,10 +2284,10 @@ struct Setup {
                 return T;
             }
         }
-        int *cnt = c.arena.alloc<int>(T.n + 1);
-        int *fill = c.arena.alloc<int>(T.n + 1);
-        zero(cnt, sizeof(int) * (T.n + 1));
-        zero(fill, sizeof(int) * (T.n + 1));
+        const size_t nz = ((size_t)T.n + 4) / 4 * 4;  // whole 16-byte units: one fill clears both
+        int *cnt = c.arena.alloc<int>(2 * nz);
+        int *fill = cnt + nz;
+        zero(cnt, 2 * nz * sizeof(int));
         int *tci = c.arena.alloc<int>(T.nnz);
         double *tv = c.arena.alloc<double>(T.nnz);
         hipLaunchKernelGGL(k_t_count, dim3(gsz(A.n)), dim3(kBlock), 0, s, A.n, A.rp, A.ci, cnt);
@@ -2289,7 +2298,6 @@ struct Setup {
         hipLaunchKernelGGL(k_row_sort, dim3(waves_g), dim3(kBlock), 0, s, T.n, T.rp, tci, tv, T.ci, T.v);
         check_kernels();
         c.arena.release(cnt);
-        c.arena.release(fill);
         c.arena.release(tci);
         c.arena.release(tv);
         return T;
@@ -2611,9 +2619,8 @@ void build_hierarchy(Ctx &c, const amg_csr &Ain, const amg_csr &Min, const uint8
     const int N = Ain.nrows;
     c.N = N;
     DCsr A = su.copy_in(Ain);
-    su.check_matrix(A, "A");
     DCsr M = su.copy_in(Min);
-    su.check_matrix(M, "M");
+    su.check_matrices(A, M);
     // Dirichlet reduction of the stiffness matrix
     Level l0;
     l0.n = N;
@@ -2785,8 +2792,9 @@ void form_dense_hessian(Ctx &c, int ell) {
     const size_t nn = (size_t)n * n;
     double *Ainv = (lv == c.L - 1) ? c.Ainv : su.dense_inverse({&L.A});
     const uint8_t *mk = lv == 0 ? L.mask : nullptr;
-    double *My = c.arena.alloc<double>(nn), *Myu = c.arena.alloc<double>(nn), *Mu = c.arena.alloc<double>(nn);
-    for (double *p : {My, Myu, Mu}) su.zero(p, sizeof(double) * nn);
+    const size_t nz = (nn + 1) / 2 * 2;  // whole 16-byte units: one fill clears all three
+    double *My = c.arena.alloc<double>(3 * nz), *Myu = My + nz, *Mu = My + 2 * nz;
+    su.zero(My, sizeof(double) * 3 * nz);
     hipLaunchKernelGGL(k_densify, dim3(gwave(n)), dim3(kBlock), 0, s, n, L.M.rp, L.M.ci, L.M.v, mk, mk, My);
     hipLaunchKernelGGL(k_densify, dim3(gwave(n)), dim3(kBlock), 0, s, n, L.M.rp, L.M.ci, L.M.v, mk,
                        (const uint8_t *)nullptr, Myu);
@@ -2797,17 +2805,15 @@ void form_dense_hessian(Ctx &c, int ell) {
     hipLaunchKernelGGL(k_gemm, gg, dim3(256), 0, s, n, Ainv, 0, Myu, X);
     hipLaunchKernelGGL(k_gemm, gg, dim3(256), 0, s, n, My, 0, X, Y);
     hipLaunchKernelGGL(k_gemm, gg, dim3(256), 0, s, n, X, 1, Y, XtY);
-    double *H = c.arena.alloc<double>(nn);
-    hipLaunchKernelGGL(k_hsym, dim3(gsz((long)nn)), dim3(kBlock), 0, s, n, XtY, Mu, c.o.beta, H);
+    double *H = c.arena.alloc<double>(nn), *Hf = c.arena.alloc<double>(nn);  // kept, and inverted
+    hipLaunchKernelGGL(k_hsym, dim3(gsz((long)nn)), dim3(kBlock), 0, s, n, XtY, Mu, c.o.beta, H, Hf);
     su.check_kernels();
-    double *Hf = c.arena.alloc<double>(nn);
-    AMG_HIP(hipMemcpyAsync(Hf, H, sizeof(double) * nn, hipMemcpyDeviceToDevice, s));
     c.Hinv = su.factor_invert(Hf, n);
     c.dH = su.dense_op(c.Hinv, n);
     c.Hdense = H;
     c.nH = n;
     c.ell = ell;
-    for (double *p : {My, Myu, Mu, X, Y, XtY}) c.arena.release(p);
+    for (double *p : {My, X, Y, XtY}) c.arena.release(p);
     if (Ainv != c.Ainv) c.arena.release(Ainv);
     su.check_flags();
 }
