@@ -199,10 +199,20 @@ struct DCsr {
     // batch, whose gathers and multiplications for a padded entry cost as much as
     // for a stored one, only up to half as many again (3D P1 rows pad by 12 %)
     bool sell_for(int nb) const { return sl_off && (nb == 1 || 2 * sl_tot <= 3L * nnz); }
+    // optional 16-bit columns of a large coarse matrix for products on one column:
+    // entry p of row i is column row_base(i, c16_scale) + c16[p] (present only when
+    // every offset fits)
+    int16_t *c16 = nullptr;
+    uint32_t c16_scale = 0;
     // lanes-per-row choice set by the autotuner: log2 G for batch width
     // 2^k (k = 0..4) and values FP64 (0) / float32 (1); -1 = the default rule
     int8_t tuned_lg[5][2] = {{-1, -1}, {-1, -1}, {-1, -1}, {-1, -1}, {-1, -1}};
 };
+
+// The column about which row i of an n x m hierarchy matrix is centred: the levels
+// are numbered alike (an aggregate's number follows its root's), so a row's columns
+// lie around i m / n; the row itself when n = m.  scale = m 2^24 / n, m < 256 n.
+__host__ __device__ inline int row_base(int i, uint32_t scale) { return (int)(((uint64_t)(uint32_t)i * scale) >> 24); }
 
 constexpr int kBlock = 256;      // threads per workgroup (4 wavefronts of 64)
 constexpr int kMaxGrid = 16384;        // workgroups at most for kernels with reductions

@@ -1446,6 +1446,19 @@ __global__ __launch_bounds__(kBlock) void k_mirror(int n, const int *rp, const i
     }
 }
 
+// 16-bit columns about row_base; an offset that does not fit sets *wide
+__global__ void k_off16(int n, const int *rp, const int *ci, uint32_t scale, int16_t *out, int *wide) {
+    const int gl = row_lane();
+    for (int i = row_first(); i < n; i += row_stride()) {
+        const int b = row_base(i, scale), e = rp[i + 1];
+        for (int p = rp[i] + gl; p < e; p += kRowLanes) {
+            const int d = ci[p] - b;
+            out[p] = (int16_t)d;
+            if (d != (int16_t)d) *wide = 1;
+        }
+    }
+}
+
 // float32 copies of several arrays in one launch (the hierarchy's copies are
 // some thirty arrays, most of them shorter than a launch is long)
 constexpr int kCopies = 16;
@@ -2495,6 +2508,19 @@ struct Setup {
         copies.n = 0;
     }
 
+    // 16-bit columns of A; whether they fit is known after make_sell's wait
+    static constexpr int kOffWord = 56, kOffMax = 8;
+    std::vector<DCsr *> off16;
+    void make_off16(DCsr &A) {
+        if ((int)off16.size() == kOffMax || A.n == 0 || A.nnz == 0 || A.m >= 256L * A.n) return;
+        if (off16.empty()) zero(isc + kOffWord, kOffMax * sizeof(int));
+        A.c16_scale = (uint32_t)(((uint64_t)A.m << 24) / (uint64_t)A.n);
+        A.c16 = c.arena.alloc<int16_t>(A.nnz);
+        hipLaunchKernelGGL(k_off16, dim3(gsz((long)A.n * kRowLanes)), dim3(kBlock), 0, s, A.n, A.rp, A.ci,
+                           A.c16_scale, A.c16, isc + kOffWord + (int)off16.size());
+        off16.push_back(&A);
+    }
+
     // sliced-ELL copies of two matrices: their widths are counted before the
     // one wait for both totals
     static constexpr int kSellWord = 48, kSellWords = 4;  // per matrix: total, wide, over8
@@ -2513,8 +2539,16 @@ struct Setup {
                                A.sl_base, w + 1, w + 2);
             scan(cnt[q], A.sl_off, A.nsl, false, w);
         }
-        AMG_HIP(hipMemcpyAsync(hisc, isc + kSellWord, 2 * kSellWords * sizeof(int), hipMemcpyDeviceToHost, s));
+        static_assert(kOffWord == kSellWord + 2 * kSellWords, "read together");
+        AMG_HIP(hipMemcpyAsync(hisc, isc + kSellWord, (2 * kSellWords + kOffMax) * sizeof(int),
+                               hipMemcpyDeviceToHost, s));
         AMG_HIP(hipStreamSynchronize(s));
+        for (size_t k = 0; k < off16.size(); ++k)
+            if (hisc[2 * kSellWords + k]) {  // 16-bit offsets do not reach
+                c.arena.release(off16[k]->c16);
+                off16[k]->c16 = nullptr;
+            }
+        off16.clear();
         for (int q = 0; q < 2; ++q) {
             DCsr &A = *mat[q];
             const int tot = hisc[q * kSellWords];
@@ -2730,6 +2764,18 @@ void build_hierarchy(Ctx &c, const amg_csr &Ain, const amg_csr &Min, const uint8
         }
     }
     su.f32_run();
+    // 16-bit columns where a product on one column is bound by its entries (the
+    // rule of long_rows, in either precision) and for a fused pass over T whose
+    // columns are past 16 bits
+    if (c.nbp == 1)
+        for (size_t l = 0; l < c.lev.size(); ++l) {
+            Level &L = c.lev[l];
+            auto large = [](const DCsr &m) { return m.rp && m.nnz > 16L * m.n && 12.0 * (double)m.nnz >= 1e7; };
+            if (l > 0 && large(L.A)) su.make_off16(L.A);
+            if (l > 0 && large(L.M)) su.make_off16(L.M);
+            if (large(L.St)) su.make_off16(L.St);
+            if (L.T.v && !L.Tc16) su.make_off16(L.T);
+        }
     // sliced-ELL copies of the finest-level A and M (rows of near-equal length;
     // the prolongator's rows vary too much for the padding to pay)
     su.make_sell(c.lev[0].A, c.lev[0].M);

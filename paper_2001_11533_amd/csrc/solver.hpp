@@ -109,13 +109,19 @@ template <int NB> struct Solver {
         const Units u = units(ceil_div(A.n, geo.rpb()), g);
         Reducer<(NV > 0 ? NV : 1), NB> red{part[pbuf]};
         if (NV > 0) pgrid[pbuf] = g;
-        auto go = [&](auto kern) {
+        auto go = [&](auto kern, auto *ci) {
             hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, s, flag(stop), u.n, u.run, u.step, A.n, geo.lg, A.rp,
-                               A.ci, vals, gx, ep, red, pro);
+                               ci, vals, gx, ep, red, pro, A.c16_scale);
         };
-        if (A.n == c.N) go(spmv_kernel<T, NB, NV, GX, EP, 1, PRO>);
-        else if (long_rows<NB, T>(A)) go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO, NB == 1 ? kSpmvUnrollLong : kSpmvUnroll>);
-        else go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO>);
+        if (A.n == c.N) {
+            go(spmv_kernel<T, NB, NV, GX, EP, 1, PRO>, A.ci);
+        } else if constexpr (NB == 1) {
+            if (!long_rows<NB, T>(A)) go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO>, A.ci);
+            else if (A.c16) go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO, kSpmvUnrollLong, int16_t>, A.c16);
+            else go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO, kSpmvUnrollLong>, A.ci);
+        } else {
+            go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO>, A.ci);
+        }
         finish<NV>(pbuf, fin, stop);
     }
 
@@ -130,12 +136,21 @@ template <int NB> struct Solver {
         const Units u = units(ceil_div(Tm.n, geo.rpb()), g);
         Reducer<(NV > 0 ? NV : 1), NB> red{part[pbuf]};
         if (NV > 0) pgrid[pbuf] = g;
-        if (Lv.Tc16)
-            hipLaunchKernelGGL((tpro_kernel<T, NB, NV, EP, uint16_t>), dim3(g), dim3(kBlock), 0, s, flag(stop), u.n,
-                               u.run, u.step, Tm.n, geo.lg, Tm.rp, Lv.Tc16, avals<T>(Tm), tsvals<T>(Lv), e, ep, red);
-        else
-            hipLaunchKernelGGL((tpro_kernel<T, NB, NV, EP>), dim3(g), dim3(kBlock), 0, s, flag(stop), u.n, u.run,
-                               u.step, Tm.n, geo.lg, Tm.rp, Tm.ci, avals<T>(Tm), tsvals<T>(Lv), e, ep, red);
+        auto go = [&](auto kern, auto *ci) {
+            hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, s, flag(stop), u.n, u.run, u.step, Tm.n, geo.lg, Tm.rp,
+                               ci, avals<T>(Tm), tsvals<T>(Lv), e, ep, red, Tm.c16_scale);
+        };
+        if (Lv.Tc16) {
+            go(tpro_kernel<T, NB, NV, EP, uint16_t>, Lv.Tc16);
+            return;
+        }
+        if constexpr (NB == 1) {
+            if (Tm.c16) {
+                go(tpro_kernel<T, NB, NV, EP, int16_t>, Tm.c16);
+                return;
+            }
+        }
+        go(tpro_kernel<T, NB, NV, EP>, Tm.ci);
     }
 
     template <int NV, class OP, class FIN> void elem(int n, OP op, FIN fin, const int *stop, int pbuf = 0) {
