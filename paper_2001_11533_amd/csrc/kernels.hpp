@@ -177,8 +177,9 @@ __host__ __device__ constexpr int ilog2(int x) {
     return l;
 }
 
-// entries a lane loads together, and in large matrices of long rows
-constexpr int kSpmvUnroll = 4, kSpmvUnrollLong = 8;
+// entries a lane loads together, and in large matrices of long rows (mid: whose
+// rows leave the slots of eight half empty)
+constexpr int kSpmvUnroll = 4, kSpmvUnrollMid = 6, kSpmvUnrollLong = 8;
 
 // Whether a one-column product on a coarse matrix takes kSpmvUnrollLong entries
 // per lane: rows of more than 16 entries, 10 MB or more of entries.  Such a
@@ -187,6 +188,12 @@ constexpr int kSpmvUnroll = 4, kSpmvUnrollLong = 8;
 // of 46 entries in FP64: 34.2 -> 25.4 us; of 33 in float32: 15.1 -> 12.2 us);
 // a smaller one is a single round that more lanes shorten (22748 rows of 32 in
 // float32: 3.5 us, 3.8 us with eight entries).
+// Every slot of a round costs its loads whether a row fills it or not, and these
+// launches are bound by the loads they issue: rows of at most 4.5 G entries, which
+// a round of six per lane still takes nearly all of, take six (184344 rows of 33,
+// G = 8: 12.7 -> 11.8 us in float32, 21.0 -> 19.2 us in FP64), longer ones eight
+// (rows of 46: 22.0 us, 27.0 with six; 38: 19.4 us, 20.5 with six).
+template <typename M> inline bool mid_rows(const M &A, int lg) { return 2L * A.nnz <= 9L * A.n << lg; }
 template <int NB, typename T> inline bool long_rows(const DCsr &A) {
     return NB == 1 && A.nnz > 16L * A.n && (4.0 + sizeof(T)) * (double)A.nnz >= 1e7;
 }

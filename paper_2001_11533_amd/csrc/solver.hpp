@@ -116,9 +116,14 @@ template <int NB> struct Solver {
         if (A.n == c.N) {
             go(spmv_kernel<T, NB, NV, GX, EP, 1, PRO>, A.ci);
         } else if constexpr (NB == 1) {
+            auto go_long = [&](auto tag) {
+                constexpr int U = decltype(tag)::value;
+                if (A.c16) go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO, U, int16_t>, A.c16);
+                else go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO, U>, A.ci);
+            };
             if (!long_rows<NB, T>(A)) go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO>, A.ci);
-            else if (A.c16) go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO, kSpmvUnrollLong, int16_t>, A.c16);
-            else go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO, kSpmvUnrollLong>, A.ci);
+            else if (mid_rows(A, geo.lg)) go_long(std::integral_constant<int, kSpmvUnrollMid>{});
+            else go_long(std::integral_constant<int, kSpmvUnrollLong>{});
         } else {
             go(spmv_kernel<T, NB, NV, GX, EP, 0, PRO>, A.ci);
         }
