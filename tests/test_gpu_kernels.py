@@ -93,19 +93,27 @@ def test_products_and_dots(n, lens, spread, nb):
             assert (np.abs(q - ref) <= 2 * (n + k) * EPS * mag).all(), which
 
 
-# a level-1 matrix of long rows beyond 10 MB in both precisions (eight entries
-# per lane), level-0 launches that sweep more rows than they have workgroups
-@pytest.fixture(scope="module")
-def big():
+# level-1 matrices of long rows beyond 10 MB in both precisions (six and eight
+# entries per lane), more than 65536 level-1 nodes, level-0 launches that sweep more
+# rows than they have workgroups; columns about the row's place (16 bits) in the
+# natural numbering, anywhere (32 bits) in a random one
+@pytest.fixture(scope="module", params=["natural", "shuffled"])
+def big(request):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import paper_2001_11533_amd as amg
-    p = inputs.config("c3", n=84)
-    rp, ci, va, vm = amg.assemble_p1(p.mesh.coords, p.mesh.elems, p.kappa)
-    gs = {nb: amg.HessianSolver((rp, ci, va), (rp, ci, vm), p.dirichlet, beta=p.beta, nb_max=nb, inner_precision=32,
+    p = inputs.config("c3", n=96)
+    coords, elems, bc = p.mesh.coords, p.mesh.elems, p.dirichlet
+    if request.param == "shuffled":
+        perm = np.random.default_rng(96).permutation(p.mesh.nverts)
+        inv = np.empty_like(perm)
+        inv[perm] = np.arange(len(perm))
+        coords, elems, bc = np.ascontiguousarray(coords[perm]), inv[elems].astype(elems.dtype), bc[perm].copy()
+    rp, ci, va, vm = amg.assemble_p1(coords, elems, p.kappa)
+    gs = {nb: amg.HessianSolver((rp, ci, va), (rp, ci, vm), bc, beta=p.beta, nb_max=nb, inner_precision=32,
                                 smoother=1) for nb in (1, 16)}
     n1, nnz1, _, _ = gs[1].level_size(1)
-    assert nnz1 > 16 * n1 and 8 * nnz1 >= 1e7
+    assert n1 > 65536 and nnz1 > 16 * n1 and 8 * nnz1 >= 1e7
     return gs
 
 
