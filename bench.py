@@ -436,7 +436,7 @@ def main():
                        "traffic": counter_traffic("cg_product_c3"),
                        "kernel": ("level-0 product of the FP64 inner CG preconditioned by float32 V-cycles, "
                                   "q = A_0 z + beta q_old with the previous iteration's finalize folded in "
-                                  "(sell_kernel<double,1,GZ<double,1,float>,ECgQR<double,1,float>,FusedFin<1,false>>)"),
+                                  "(sell_kernel<double,1,1,GZ<double,1,float>,ECgQR<double,1,float>,FusedFin<1,false>,8>)"),
                        "ms": cgp_ms, "bytes": cgp_bytes,
                        "bytes_rule": "4(n+1) + (4+8) nnz(A_0) + 2*8 n: the method's q = A_0 p, FP64, int32 columns",
                        "timing": ("HIP events on the library stream over 200 back-to-back launches that rotate "
@@ -454,7 +454,7 @@ def main():
                      "unit": "GB/s", "frac": pre_bytes / (pre_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                      "traffic": counter_traffic("sell_presweep_c3"),
                      "kernel": ("level-0 float32 pre-sweep residual r = b - A x of the V-cycle "
-                                "(sell_kernel<float,0,GPlain,EResB>)"),
+                                "(sell_kernel<float,1,0,GPlain,EResB>)"),
                      "ms": pre_ms, "bytes": pre_bytes,
                      "bytes_rule": ("4(n+1) + (2+4) nnz(A_0) + 3*4 n: r = b - A_0 x, float32, counted with the 16-bit "
                                     "column offsets the sliced-ELL level-0 matrix stores (int32 columns: 33.8 MB)"),

@@ -229,7 +229,7 @@ constexpr int kXcd = 8;          // XCDs of an MI355X
 __host__ __device__ inline int ceil_div(long a, long b) { return (int)((a + b - 1) / b); }
 
 // Grid for a row-blocked kernel: a multiple of 8 so that the XCD-aware remap
-// (see xcd_block) is a permutation.
+// (see xcd_share) is a permutation.
 inline int grid_rows(long rows, int rows_per_block, int maxg = kMaxGrid) {
     int g = ceil_div(rows, rows_per_block);
     if (g > maxg) g = maxg;

@@ -3,18 +3,18 @@
 // two-stage grid reductions, and the dense coarse-level apply.
 //
 // Layout: every work vector is row-major [n x NB] (entry (i, c) at i*NB + c),
-// NB in {1, 2, 4, 8, 16}.  A row of a CSR matrix is handled by LPR =
-// max(8, NB) consecutive lanes of one wavefront: lane l works on column
-// c = l % NB and on the stored entries g, g + G, ... of the row, g = l / NB,
-// G = LPR / NB; the G partial sums are combined with wavefront shuffles.
-// For NB >= 8 every lane owns one column and the NB lanes of a row read the
-// same (col, val) entry, so the matrix is fetched once per row for all
-// right-hand sides while the x gathers are NB-contiguous.
+// NB in {1, 2, 4, 8, 16}.  A row of a CSR matrix is handled by LPR = G NG
+// consecutive lanes of one wavefront: NG = NB / CV groups of CV columns (CV = 1,
+// 2 or 4 columns per lane, read as one contiguous piece), times G lanes that take
+// the stored entries g, g + G, ... of the row; the G partial sums are combined
+// across the lanes.  Every (column, value) entry is fetched once per row and
+// column group for CV right-hand sides.
 //
 // Reductions are deterministic: each workgroup reduces its contribution in a
-// fixed LDS tree and writes one partial per (quantity, column); a one-workgroup
-// kernel launched next sums the partials in a fixed order and runs a small
-// "finalize" step on thread 0 (CG scalars, convergence flags).  Issuing a
+// fixed tree and writes one partial per (quantity, column); a one-workgroup
+// kernel launched next (or the prologue of the next kernel that needs the
+// result) sums the partials in a fixed order and runs a small "finalize" step, a
+// thread per column (CG scalars, convergence flags).  Issuing a
 // device-scope fence per workgroup instead (a "last workgroup" ticket) makes
 // every workgroup write back its XCD's L2 and costs far more than the launch.
 #pragma once
@@ -188,15 +188,16 @@ constexpr int kSpmvUnroll = 4, kSpmvUnrollMid = 6, kSpmvUnrollLong = 8;
 // of 46 entries in FP64: 34.2 -> 25.4 us; of 33 in float32: 15.1 -> 12.2 us);
 // a smaller one is a single round that more lanes shorten (22748 rows of 32 in
 // float32: 3.5 us, 3.8 us with eight entries).
+template <int NB, typename T> inline bool long_rows(const DCsr &A) {
+    return NB == 1 && A.nnz > 16L * A.n && (4.0 + sizeof(T)) * (double)A.nnz >= 1e7;
+}
+
 // Every slot of a round costs its loads whether a row fills it or not, and these
 // launches are bound by the loads they issue: rows of at most 4.5 G entries, which
 // a round of six per lane still takes nearly all of, take six (184344 rows of 33,
 // G = 8: 12.7 -> 11.8 us in float32, 21.0 -> 19.2 us in FP64), longer ones eight
 // (rows of 46: 22.0 us, 27.0 with six; 38: 19.4 us, 20.5 with six).
 template <typename M> inline bool mid_rows(const M &A, int lg) { return 2L * A.nnz <= 9L * A.n << lg; }
-template <int NB, typename T> inline bool long_rows(const DCsr &A) {
-    return NB == 1 && A.nnz > 16L * A.n && (4.0 + sizeof(T)) * (double)A.nnz >= 1e7;
-}
 
 // The fixed rule for G, from the mean row length m (measured over G = 1 .. 64 on
 // every product of 2D and 3D hierarchies of 7e4 to 2.1e6 rows, 1 to 16 columns):
