@@ -1926,8 +1926,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) 
 // of the rows in turn, each chunk four v_mfma_f64_16x16x4f64 (lane l: row l % 16,
 // the entries 4 (l / 16) .. + 3 of the chunk in one 16-byte load per four floats;
 // step e multiplies entry e of each lane, so the matrix operand's k and the
-// batch operand's k are permuted alike), eight (float32) or four chunks' loads
-// in flight, and their sums are added through LDS in wavefront order.  The
+// batch operand's k are permuted alike), the loads of D chunks in flight, and their
+// sums are added through LDS in wavefront order.  The
 // accumulation is FP64 whatever T.  Lanes past `rows`, columns past NB and rows
 // past n are computed from clamped reads and dropped; chunks past the last are
 // zeroed (rows are zero-padded to ld, so the ragged chunk needs only its batch
@@ -1936,7 +1936,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) 
 // the lanes past it is not what is waited for.  n = 1639, float32, 16 columns:
 // 9.2 us with 8 rows per workgroup, 9.5 us with 16 (103 workgroups), 29.2 us
 // with a wavefront per row on the vector ALUs, whose lanes each read every
-// column of the batch.
+// column of the batch.  Slots past a wavefront's chunks cost their loads, so D is
+// the chunks it has, up to eight (float32) or four: 597 rows, float32, 8 columns:
+// 4.6 us with three, 9.0 us with eight; 149 rows, FP64, 16 columns: 3.6 us with one,
+// 4.8 us with four.
 inline int dense_mm_rows(int n) {
     int r = 1;
     while (r < 16 && ceil_div(n, r) > 256) r <<= 1;
@@ -1944,14 +1947,13 @@ inline int dense_mm_rows(int n) {
 }
 constexpr int kMmWaves = 16;
 typedef double mm_v4d __attribute__((ext_vector_type(4)));
-template <typename T, int NB>
+template <typename T, int NB, int D>
 __global__ __launch_bounds__(64 * kMmWaves) void dense_mm_kernel(const int *__restrict__ stop, int n, int ld,
                                                                  int rows, const T *__restrict__ inv,
                                                                  const T *__restrict__ b, T *__restrict__ x) {
     const int st = *stop;  // tested before the store: no load waits for it
     using V = Vec16<T>;
     using VT = typename V::type;
-    constexpr int D = sizeof(T) == 4 ? 8 : 4;
     const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, kq = (l >> 4) * 4;
     const int row0 = blockIdx.x * rows;
     const T *row = inv + (size_t)min(row0 + min(l & 15, rows - 1), n - 1) * ld;

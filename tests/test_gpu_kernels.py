@@ -41,9 +41,10 @@ def solver(A, M, mask=None, **opts):
 
 
 # one column and up to four run on vector ALUs (a wavefront per row), more on
-# the matrix cores (1, 2, 8 or 16 rows per workgroup at these sizes)
+# the matrix cores (1, 2, 4, 8 or 16 rows per workgroup and one, two, three, four or
+# eight chunks of loads per wavefront at these sizes)
 @pytest.mark.parametrize("nb", [1, 2, 3, 4, 7, 16])
-@pytest.mark.parametrize("n", [2, 15, 17, 64, 257, 1030, 2049])
+@pytest.mark.parametrize("n", [2, 15, 17, 64, 257, 600, 1000, 1030, 2049])
 def test_dense_inverse_apply(n, nb):
     g = solver(chain(n), chain(n), nb_max=nb, inner_precision=32, max_coarse=n, dense_max=4096)
     assert g.levels()[0] == 1
