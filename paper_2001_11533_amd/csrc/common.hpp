@@ -186,7 +186,7 @@ struct DCsr {
     // by column, entry k of row 64 s + l at sl_off[s] + 64 k + l; a column is
     // kept as a 16-bit offset from the slice's smallest column sl_base[s] (the
     // copy exists only when every slice spans fewer than 65536 columns), and the
-    // rows of a slice are padded to its longest with (offset 0, value 0)
+    // rows of a slice are padded to its longest with (the row's last offset, value 0)
     int nsl = 0;
     long sl_tot = 0;        // stored entries, padding included
     bool sl_over8 = true;   // some slice is wider than 8 entries per row

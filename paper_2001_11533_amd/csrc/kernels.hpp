@@ -757,7 +757,7 @@ __global__ __launch_bounds__(kBlock) void sell_kernel(const int *__restrict__ st
             // its last entry again, weighted by 0), so the U column and value
             // loads, then the U gathers, are in flight together; guarded loads
             // compile to one wait per entry.  A weight of exactly 0 leaves the
-            // sum unchanged.
+            // sum unchanged, and gathers what the row's last entry gathers.
             int kk[U];
             T aa[U];
 #pragma unroll

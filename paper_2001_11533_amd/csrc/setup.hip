@@ -1797,7 +1797,10 @@ __global__ void k_sell_width(int n, int nsl, const int *rp, const int *ci, int *
 // kSellStage of them is read in order into LDS (a lane reading its own row
 // strides through memory by the row length) and written from there, with the
 // float32 values when sv32 is given.  Bound by memory: 274625 rows of 15
-// entries 98 + 5 us (values, then float32) before, 43 us now.
+// entries 98 + 5 us (values, then float32) before, 43 us now.  A row is padded to
+// the slice's width with its own last column and the value 0, so that a product
+// gathers nothing for it but what the row holds (0 times an infinity or a NaN
+// elsewhere would reach the row).
 constexpr int kSellStage = 1024;
 __global__ __launch_bounds__(kBlock) void k_sell_fill(int n, int nsl, const int *rp, const int *ci, const double *v,
                                                       const int *soff, const int *base, uint16_t *scd, double *sv,
@@ -1820,9 +1823,10 @@ __global__ __launch_bounds__(kBlock) void k_sell_fill(int n, int nsl, const int 
             }
             wave_sync();
         }
+        const uint16_t pad = len == 0 ? 0 : staged ? lc[wv][p0 - first + len - 1] : (uint16_t)(ci[p0 + len - 1] - b);
         for (int k = 0; k < wd; ++k) {
             const size_t q = (size_t)o + (size_t)k * 64 + lane;
-            uint16_t cd = 0;
+            uint16_t cd = pad;
             double x = 0.0;
             if (k < len) {
                 cd = staged ? lc[wv][p0 - first + k] : (uint16_t)(ci[p0 + k] - b);

@@ -206,3 +206,49 @@ def test_unaligned_and_overlapping_vectors(nb, shift):
             a, b = f(z), f(aligned)
             assert torch.linalg.norm(a - b) <= 1e-12 * torch.linalg.norm(b), f
             assert torch.equal(z, aligned)
+
+
+def stencil(n, offs, seed):
+    """symmetric, the diagonals 0, +-offs with every tenth entry missing: rows of unequal
+    length, in slices of 64 that pad by little"""
+    rng = np.random.default_rng(seed)
+    m = sp.diags([np.where(rng.random(max(n - o, 0)) < 0.9, rng.uniform(0.5, 1.0, max(n - o, 0)), 0.0) for o in offs],
+                 list(offs), shape=(n, n)).tocsr()
+    m.eliminate_zeros()
+    return (m + m.T + 40.0 * sp.eye(n)).tocsr()
+
+
+def padding(M):
+    """entries of the sliced-ELL copy over stored entries"""
+    k = np.diff(M.indptr)
+    return sum(64 * k[s:s + 64].max() for s in range(0, len(k), 64)) / M.nnz
+
+
+# a value that is not finite reaches the rows that hold its node and no others,
+# whatever entries a matrix copy pads its rows with: single values at the smallest
+# column of a slice of 64 rows.  Rows of at most eight and of more entries in sliced
+# ELL at every width, a few long rows on CSR for batches
+@pytest.mark.parametrize("nb", [1, 2, 3, 4, 8, 16])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("n,offs", [(64, (1, 5, 9)), (127, (1, 5, 9)), (1000, (1, 30, 31)), (5000, range(1, 9)),
+                                    (3001, None)])
+def test_products_keep_non_finite_values_to_their_rows(n, offs, bad, nb):
+    if offs:
+        M = stencil(n, offs, n)
+        assert padding(M) <= 1.5
+    else:
+        M = banded(n, [1] * 40 + [70], 1200, n)
+        assert padding(M) > 1.5
+    M.sort_indices()
+    g = solver(chain(n), M, nb_max=nb, max_coarse=64)
+    x = np.random.default_rng(nb).standard_normal((n, nb))
+    x0, hit = x.copy(), np.zeros((n, nb), dtype=bool)
+    for sl, c in ((0, 0), ((n - 1) // 64 // 2, nb - 1)):
+        k = M.indices[M.indptr[64 * sl]:M.indptr[min(64 * (sl + 1), n)]].min()
+        x[k, c], x0[k, c] = bad, 0.0
+        hit[M.indices[M.indptr[k]:M.indptr[k + 1]], c] = True  # M is symmetric: row k holds the column's rows
+    y = g.mass_apply(cuda(x)).cpu().numpy()
+    assert (np.isnan(y[hit]) if np.isnan(bad) else ~np.isfinite(y[hit])).all()
+    k = np.diff(M.indptr).max() + 2
+    err = np.abs(np.where(hit, 0.0, y - M @ x0))
+    assert (err <= 2 * k * EPS * (abs(M) @ np.abs(x0))).all()
