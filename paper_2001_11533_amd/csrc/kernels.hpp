@@ -1929,9 +1929,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) 
 // batch operand's k are permuted alike), the loads of D chunks in flight, and their
 // sums are added through LDS in wavefront order.  The
 // accumulation is FP64 whatever T.  Lanes past `rows`, columns past NB and rows
-// past n are computed from clamped reads and dropped; chunks past the last are
-// zeroed (rows are zero-padded to ld, so the ragged chunk needs only its batch
-// index clamped).  Bound by the latency of the matrix's and the batch's loads:
+// past n are computed from clamped reads and dropped; the batch's entries past n
+// (the ragged chunk's, and those of chunks past the last, which re-read it) are
+// zeroed: the matrix's entries there are finite, the batch's need not be.  Bound by the latency of the matrix's and the batch's loads:
 // `rows` is what fills the 256 CUs (dense_mm_rows), matrix-core work done for
 // the lanes past it is not what is waited for.  n = 1639, float32, 16 columns:
 // 9.2 us with 8 rows per workgroup, 9.5 us with 16 (103 workgroups), 29.2 us
@@ -1974,11 +1974,11 @@ __global__ __launch_bounds__(64 * kMmWaves) void dense_mm_kernel(const int *__re
         __builtin_amdgcn_sched_barrier(0);  // the loads stay together, ahead of their uses
 #pragma unroll
         for (int u = 0; u < D; ++u) {
-            const bool on = c0 + u * kMmWaves < nk;
+            const int k = (c0 + u * kMmWaves) * 16 + kq;  // past n in the chunks past the last
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const double a = on ? V::get(m[u][e / V::n], e % V::n) : 0.0;
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)v[u][e], acc, 0, 0, 0);
+                const T bk = k + e < n ? v[u][e] : T(0);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(V::get(m[u][e / V::n], e % V::n), (double)bk, acc, 0, 0, 0);
             }
         }
     }

@@ -252,3 +252,20 @@ def test_products_keep_non_finite_values_to_their_rows(n, offs, bad, nb):
     k = np.diff(M.indptr).max() + 2
     err = np.abs(np.where(hit, 0.0, y - M @ x0))
     assert (err <= 2 * k * EPS * (abs(M) @ np.abs(x0))).all()
+
+
+# ... and an infinity in a dense solve's right-hand side, where every product with it
+# is infinite (a tridiagonal M-matrix has a positive inverse), leaves infinities
+@pytest.mark.parametrize("nb", [1, 4, 7, 16])
+@pytest.mark.parametrize("n", [15, 64, 257, 600])
+@pytest.mark.parametrize("prec", [32, 64])
+def test_dense_apply_of_infinities(n, nb, prec):
+    g = solver(chain(n), chain(n), nb_max=nb, inner_precision=32, max_coarse=n, dense_max=4096)
+    inv = g.dense(0).astype(np.float32 if prec == 32 else np.float64).astype(np.float64)
+    assert (inv > 0).all()
+    for k in (0, n - 2, n - 1):
+        b = np.random.default_rng(n + nb).standard_normal((n, nb))
+        b[k, 0] = np.inf
+        x = g.vcycle_apply(cuda(b), prec=prec).cpu().numpy()
+        assert (x[:, 0] == np.inf).all()
+        assert np.isfinite(x[:, 1:]).all()
