@@ -36,6 +36,10 @@
  *   - Every call enqueues its work on the stream given to amg_setup and
  *     returns once its outputs are valid on that stream (calls that test
  *     convergence synchronise on a few scalars).
+ *   - After an error (HIP aside) a call's vector outputs are what they were
+ *     before it, with one exception: reduced_solve writes the outer CG's last
+ *     iterate to u when that iteration ends without converging (NOCONV at
+ *     outer_maxit, INDEFINITE).
  *   - A context is not thread-safe; use one context per host thread.
  *   - Every public vector is FP64 whatever opts.inner_precision is.
  */
@@ -53,7 +57,7 @@ extern "C" {
 #define AMG_ERR_ARG (-1)            /* invalid argument (null, size, range) */
 #define AMG_ERR_NOT_SYMMETRIC (-2)  /* input stiffness/mass matrix not exactly symmetric */
 #define AMG_ERR_NOT_SPD (-3)        /* non-positive diagonal / non-positive pivot of a dense inverse */
-#define AMG_ERR_NOCONV (-4)         /* an iteration hit its limit; outputs hold the last iterate */
+#define AMG_ERR_NOCONV (-4)         /* an iteration hit its limit, broke down or stagnated */
 #define AMG_ERR_INDEFINITE (-5)     /* outer CG met p.Hp <= 0 or r.Br <= 0 */
 #define AMG_ERR_HIP (-6)            /* a HIP runtime call failed */
 #define AMG_ERR_OOM (-7)            /* device allocation failed */

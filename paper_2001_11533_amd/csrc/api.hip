@@ -166,7 +166,8 @@ double ms_since(clk::time_point t0) {
 // The caller's vectors as [n x NB] ones: used in place when the batch has no
 // padding columns (and an input does not overlap the output), else packed into
 // and unpacked from the context's buffers, a launch and a pass over the vector
-// each.
+// each.  An output is used in place only by a call whose last product alone
+// writes it, behind every step that can fail.
 template <int NB>
 const double *vec_in(Solver<NB> &S, int n, const double *v, double *buf, int nb, const double *out,
                      bool in_place = true) {
@@ -660,9 +661,10 @@ int state_solve(amg_ctx *ctx, int level, const double *u, double *y, int nb, amg
         return dispatch_nb(c.nbp, [&](auto tag) {
             constexpr int NB = decltype(tag)::value;
             Solver<NB> S(c);
-            const double *in = vec_in(S, n, u, c.pk_in, nb, y);
-            S.state_solve(level, in, vec_out<NB>(y, c.pk_out, nb), c.o.inner_rtol);
-            vec_done(S, n, y, c.pk_out, nb);
+            // the solve's iterate is its output: kept apart, so that y changes only
+            // when the solve has succeeded
+            S.state_solve(level, vec_in(S, n, u, c.pk_in, nb, nullptr), c.pk_out, c.o.inner_rtol);
+            S.template elem<0>(n, OpUnpack<NB>{y, c.pk_out, nb}, NoFin{}, nullptr);
             AMG_HIP(hipStreamSynchronize(c.stream));
             fill_info(c, info, 1, ms_since(t0), 0);
             return AMG_OK;

@@ -269,3 +269,18 @@ def test_dense_apply_of_infinities(n, nb, prec):
         x = g.vcycle_apply(cuda(b), prec=prec).cpu().numpy()
         assert (x[:, 0] == np.inf).all()
         assert np.isfinite(x[:, 1:]).all()
+
+
+# an inner solve that does not converge leaves the output as it was
+@pytest.mark.parametrize("nb", [1, 2, 3, 4])
+@pytest.mark.parametrize("mode", [{}, {"inner_precision": 32}, {"inner_precision": 32, "mixed_mode": 1}])
+def test_outputs_after_a_failed_inner_solve(nb, mode):
+    from paper_2001_11533_amd._lib import lib
+    n = 1501
+    g = solver(chain(n), banded(n, [4], 90, 5), nb_max=nb, max_coarse=64, dense_solve_max=0, inner_maxit=1, **mode)
+    x = cuda(np.random.default_rng(1).standard_normal((n, nb)))
+    y = torch.full_like(x, -7.0)
+    for f in (lib().state_solve, lib().adjoint_solve, lib().hessian_apply):
+        assert f(g._h, 0, x.data_ptr(), y.data_ptr(), nb, None) == -4
+        torch.cuda.synchronize()
+        assert bool((y == -7.0).all())
