@@ -683,7 +683,7 @@ int adjoint_solve(amg_ctx *ctx, int level, const double *w, double *z, int nb, a
         return dispatch_nb(c.nbp, [&](auto tag) {
             constexpr int NB = decltype(tag)::value;
             Solver<NB> S(c);
-            // a dense solve reads its right-hand side in whole vectors, past n
+            // a dense solve reads its right-hand side in whole aligned vectors, past n
             const bool dense = level == c.L - 1 || c.lev[level].Ainv;
             const double *in = vec_in(S, n, w, c.pk_in, nb, z, !dense);
             S.adjoint_solve(level, in, vec_out<NB>(z, c.pk_out, nb), c.o.inner_rtol);

@@ -25,9 +25,6 @@
 
 namespace amg {
 
-__device__ __forceinline__ int ceil_div_dev(int a, int b) { return (a + b - 1) / b; }
-__device__ __forceinline__ long ceil_div_dev_l(long a, long b) { return (a + b - 1) / b; }
-
 // ---------------------------------------------------------------------------
 // per-column CG state kept in device memory
 struct ColScal {
@@ -917,18 +914,6 @@ template <typename T, int NB> struct GPlain {  // x_k
     __device__ T operator()(int k, int c) const { return x[(size_t)k * NB + c]; }
 };
 
-template <typename T, int NB, typename TZ = T> struct GZBP {  // p_k = z_k + beta_c pold_k
-    const TZ *z;
-    const T *pold;
-    const CgScal *sc;
-    T beta;
-    __device__ void prep(int c) { beta = (T)sc->s[c].beta; }
-    __device__ void set_beta(double b) { beta = (T)b; }
-    __device__ T operator()(int k, int c) const {
-        return (T)z[(size_t)k * NB + c] + beta * pold[(size_t)k * NB + c];
-    }
-};
-
 // z_k alone: the CG product formed as A z + beta q_old (ECgQR)
 template <typename T, int NB, typename TZ = T> struct GZ {
     const TZ *z;
@@ -1248,32 +1233,6 @@ template <typename T, int NB, bool DOT> struct EProJac {
     }
 };
 
-// CG search direction and operator: p_i = z_i + beta pold_i, q_i = (A p)_i, acc p.q
-template <typename T, int NB, typename TZ = T> struct ECgQ {
-    const TZ *z;
-    const T *pold;
-    T *p;
-    T *q;
-    const CgScal *sc;
-    T beta;
-    struct P {
-        T z, po;
-    };
-    __device__ void prep(int c) { beta = (T)sc->s[c].beta; }
-    __device__ void set_beta(double b) { beta = (T)b; }
-    __device__ P load(int i, int c) const {
-        const size_t o = (size_t)i * NB + c;
-        return {(T)z[o], pold[o]};
-    }
-    template <int NV> __device__ void operator()(int i, int c, T s, const P &pr, double (&acc)[NV]) const {
-        const size_t o = (size_t)i * NB + c;
-        const T pi = pr.z + beta * pr.po;
-        p[o] = pi;
-        q[o] = s;
-        acc[0] += (double)pi * (double)s;
-    }
-};
-
 // CG direction and its product without gathering the direction:
 // p_i = z_i + beta pold_i and q_i = (A z)_i + beta qold_i, which is (A p)_i
 // since qold = A pold; q is updated in place (row i reads and writes only its
@@ -1579,31 +1538,6 @@ template <typename T, int NB, bool JAC> struct OpInit {
     }
 };
 
-template <typename T, int NB, bool JAC> struct OpUpd {  // x += a p, r -= a q (Jacobi: z = dinv r)
-    T *x, *r, *z;
-    const T *p, *q, *dinv;
-    const CgScal *sc;
-    T a;
-    int live;
-    __device__ void prep(int c) {
-        a = (T)sc->s[c].alpha;
-        live = !sc->s[c].conv;
-    }
-    template <int NV> __device__ void operator()(int i, int c, double (&acc)[NV]) const {
-        if (!live) return;
-        const size_t o = (size_t)i * NB + c;
-        x[o] += a * p[o];
-        const T rv = r[o] - a * q[o];
-        r[o] = rv;
-        acc[0] += (double)rv * (double)rv;
-        if constexpr (JAC) {
-            const T zz = dinv[i] * rv;
-            z[o] = zz;
-            acc[1] += (double)rv * (double)zz;
-        }
-    }
-};
-
 template <int NB> struct OpDot {  // acc[v] += x_v . y_v (up to 2 pairs)
     const double *x0, *y0, *x1, *y1;
     __device__ void prep(int) {}
@@ -1858,8 +1792,9 @@ template <> struct Vec16<float> {
     }
 };
 
-// At most four columns with b of the matrix's type and 16-byte aligned: b is
-// read in 16-byte vectors like the matrix rows, NB of them per vector of the
+// At most four columns, b of the matrix's type and 16-byte aligned (a workspace,
+// whose storage is allocated in 256-byte units; callers' vectors are packed into
+// one): b is read in 16-byte vectors like the matrix rows, NB of them per vector of the
 // row, eight (four with four columns) row vectors and theirs in flight per lane
 // (a float32 row of up to 2048 entries is one round).  Every load is
 // unconditional (guarded loads compile to a wait each): vectors past the last

@@ -208,24 +208,21 @@ template <int NB> struct Solver {
         // which is ahead from eight on (a lane's loads grow with the columns: 597
         // rows in float32 4.6 us against 5.7, 886 in FP64 6.4 against 10.2)
         if constexpr (NB <= 4) {
-            if (reinterpret_cast<uintptr_t>(b) % 16 == 0) {
-                hipLaunchKernelGGL((dense_vec_kernel<T, NB>), dim3(ceil_div((long)d.n * 64, kBlock)), dim3(kBlock), 0,
-                                   s, flag(stop), d.n, d.ld, m, b, x);
-                return;
-            }
+            hipLaunchKernelGGL((dense_vec_kernel<T, NB>), dim3(ceil_div((long)d.n * 64, kBlock)), dim3(kBlock), 0, s,
+                               flag(stop), d.n, d.ld, m, b, x);
+        } else {
+            auto mm = [&](auto kern) {
+                hipLaunchKernelGGL(kern, dim3(ceil_div(d.n, dense_mm_rows(d.n))), dim3(64 * kMmWaves), 0, s,
+                                   flag(stop), d.n, d.ld, dense_mm_rows(d.n), m, b, x);
+            };
+            const int per = ceil_div(ceil_div(d.n, 16), kMmWaves);  // chunks per wavefront
+            constexpr int deep = sizeof(T) == 4 ? 8 : 4;
+            if (per <= 1) mm(dense_mm_kernel<T, NB, 1>);
+            else if (per <= 2) mm(dense_mm_kernel<T, NB, 2>);
+            else if (per <= 3) mm(dense_mm_kernel<T, NB, 3>);
+            else if (per <= 4 || deep == 4) mm(dense_mm_kernel<T, NB, 4>);
+            else mm(dense_mm_kernel<T, NB, deep>);
         }
-        auto mm = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3(ceil_div(d.n, dense_mm_rows(d.n))), dim3(64 * kMmWaves), 0, s, flag(stop),
-                               d.n, d.ld, dense_mm_rows(d.n), m, b, x);
-        };
-        const int per = ceil_div(ceil_div(d.n, 16), kMmWaves);  // chunks per wavefront
-        constexpr int deep = sizeof(T) == 4 ? 8 : 4;
-        if constexpr (NB <= 4) mm(dense_mm_kernel<T, NB, deep>);
-        else if (per <= 1) mm(dense_mm_kernel<T, NB, 1>);
-        else if (per <= 2) mm(dense_mm_kernel<T, NB, 2>);
-        else if (per <= 3) mm(dense_mm_kernel<T, NB, 3>);
-        else if (per <= 4 || deep == 4) mm(dense_mm_kernel<T, NB, 4>);
-        else mm(dense_mm_kernel<T, NB, deep>);
     }
 
     void read_sc(const CgScal *d) {
