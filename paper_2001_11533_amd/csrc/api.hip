@@ -571,8 +571,8 @@ int amg_setup(const amg_csr *A, const amg_csr *M, const uint8_t *dirichlet, cons
     Range rg("amg_setup");
     int rc = guarded(nullptr, [&]() {
         c.lev.reserve(o.max_levels + 1);
-        for (auto &p : c.part) p = c.arena.alloc<double>((size_t)2 * 16 * kMaxGrid);
-        for (auto &p : c.part2) p = c.arena.alloc<double>((size_t)2 * 16 * kMaxGrid);
+        for (auto &p : c.part) p = c.arena.alloc<double>(kMaxPart);
+        for (auto &p : c.part2) p = c.arena.alloc<double>(kMaxPart);
         c.dscratch = c.arena.alloc<double>(64);
         c.iscratch = c.arena.alloc<int>(64);
         c.iscratch2 = c.arena.alloc<int>(64);
@@ -1088,8 +1088,8 @@ int amg_time_kernel(amg_ctx *ctx, int which, int prec, int nb, int reps, double 
             const double sz = prec == 64 ? 8.0 : 4.0;
             const double nbd = NB;
             // algorithmic bytes: row pointers, (col, val) per stored entry, x read
-            // once, y written once (per column); a column takes 2 bytes in the
-            // level-0 sliced-ELL copy (single column), else 4
+            // once, y written once (per column); a column takes 2 bytes where level
+            // 0's product runs on the sliced-ELL copy, else 4
             auto ib = [&](int l) { return l == 0 && c.lev[0].A.sell_for(NB) ? 2.0 : 4.0; };
             const double spmv_b = 4.0 * (n + 1) + (ib(0) + sz) * L0.A.nnz + 2.0 * sz * n * nbd;
             hipEvent_t e0, e1;
@@ -1153,7 +1153,7 @@ int amg_time_kernel(amg_ctx *ctx, int which, int prec, int nb, int reps, double 
                     const int g = grid_rows((long)n * NB, kBlock, red_grid_max<NB>());
                     S.pgrid[1] = g;
                     S.pgrid[2] = S.template red_grid<float>(L0.A);
-                    std::vector<double> ones((size_t)2 * 16 * kMaxGrid, 1.0);
+                    std::vector<double> ones(kMaxPart, 1.0);
                     AMG_HIP(hipMemcpyAsync(c.part[1], ones.data(), ones.size() * sizeof(double),
                                            hipMemcpyHostToDevice, c.stream));
                     AMG_HIP(hipMemcpyAsync(c.part[2], ones.data(), ones.size() * sizeof(double),

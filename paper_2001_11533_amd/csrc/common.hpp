@@ -215,14 +215,18 @@ struct DCsr {
 __host__ __device__ inline int row_base(int i, uint32_t scale) { return (int)(((uint64_t)(uint32_t)i * scale) >> 24); }
 
 constexpr int kBlock = 256;      // threads per workgroup (4 wavefronts of 64)
-constexpr int kMaxGrid = 16384;        // workgroups at most for kernels with reductions
-constexpr int kMaxGridPlain = 1 << 20; // and for kernels without
-// Workgroups of a reducing launch on NB columns at most: about what is resident
-// at once (four per CU at the registers of the FP64 products), each sweeping its
-// share.  Few partials keep the finalize folded into the next product: with up
-// to 16384 workgroups for one column, a CG iteration on 184344 rows took two
-// finalize launches more (4.7 + 4.2 us), one on 2.1e6 rows too.
+constexpr int kMaxGrid = 16384;        // workgroups times columns at most for kernels with reductions
+constexpr int kMaxGridPlain = 1 << 20; // workgroups at most for kernels without
+// Workgroups of a reducing launch on NB columns at most, each sweeping its share.
+// One or two columns take 1024, about what is resident at once (four per CU at the
+// registers of the FP64 products): few partials keep the finalize folded into the
+// next product (with up to 16384 workgroups for one column, a CG iteration on 184344
+// rows took two finalize launches more, 4.7 + 4.2 us, one on 2.1e6 rows too).  More
+// columns take kMaxGrid / NB, 16, 8 and 4 per CU for 4, 8 and 16: at most kMaxGrid
+// partials per quantity, which finalize launches sum.  Fewer for 4 and 8 columns have
+// not been measured.
 template <int NB> constexpr int red_grid_max() { return NB <= 2 ? 1024 : kMaxGrid / NB; }
+constexpr int kMaxPart = 2 * kMaxGrid;  // partials of a reducing launch at most: two quantities
 constexpr int kFinBlock = 1024;        // threads of a finalize kernel
 constexpr int kXcd = 8;          // XCDs of an MI355X
 
@@ -230,7 +234,7 @@ __host__ __device__ inline int ceil_div(long a, long b) { return (int)((a + b - 
 
 // Grid for a row-blocked kernel: a multiple of 8 so that the XCD-aware remap
 // (see xcd_share) is a permutation.
-inline int grid_rows(long rows, int rows_per_block, int maxg = kMaxGrid) {
+inline int grid_rows(long rows, int rows_per_block, int maxg) {
     int g = ceil_div(rows, rows_per_block);
     if (g > maxg) g = maxg;
     if (g < 1) g = 1;

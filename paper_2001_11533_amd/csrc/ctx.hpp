@@ -154,7 +154,7 @@ struct Ctx {
     int nH = 0;
     DenseOp dAc, dH;  // padded apply copies of Ainv and Hinv
     // reductions (one stream: a single partial buffer and ticket suffice)
-    double *part[3] = {nullptr, nullptr, nullptr};  // reduction partials [2*16*kMaxGrid] each
+    double *part[3] = {nullptr, nullptr, nullptr};  // reduction partials [kMaxPart] each
     int pgrid[3] = {0, 0, 0};                       // workgroups that wrote each buffer
     double *dscratch = nullptr;  // small device scalars [64]
     char *pinned = nullptr;      // the pinned block that holds the host words below

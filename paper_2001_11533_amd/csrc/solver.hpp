@@ -75,6 +75,9 @@ template <int NB> struct Solver {
     // the word a kernel tests before it writes: the CG's flag, or one that stays zero
     const int *flag(const int *stop) const { return stop ? stop : c.never; }
 
+    // what a reducing launch leaves fits a buffer of partials
+    static_assert(2 * NB * red_grid_max<NB>() <= kMaxPart && red_grid_max<NB>() % kXcd == 0, "kMaxPart");
+
     // workgroups of a reducing product with A (the partials it leaves)
     template <typename T> int red_grid(const DCsr &A) const {
         if (A.sell_for(NB)) return grid_rows(A.nsl, sell_slices<NB>(), red_grid_max<NB>());
