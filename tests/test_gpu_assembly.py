@@ -118,3 +118,76 @@ def test_rows_at_the_limits_of_the_row_kernels(dim, k, degenerate):
                                                            dev(kappa, torch.float64))]
     for a, b in zip(got, ref):
         assert np.array_equal(a, b, equal_nan=a.dtype == np.float64)
+
+
+# a plan serves any number of fills: new coordinates and coefficients, then the first
+# ones again, each against the host assembler; the ring's hub has more elements than
+# the row kernels hold, so its fills also sort the plan's lists
+@pytest.mark.parametrize("kind", ["2d", "3d", "ring2", "ring3", "loose"])
+def test_a_plan_fills_repeatedly(kind):
+    _need_gpu()
+    import paper_2001_11533_amd as amg
+    from paper_2001_11533_amd._lib import check, lib
+    L = lib()
+    if kind.startswith("ring"):
+        coords, elems, kappa = ring_mesh(int(kind[4]), 100)
+    else:
+        m = inputs.mesh2d(9) if kind == "2d" else inputs.mesh3d(5)
+        coords, elems, kappa = m.coords, m.elems.astype(np.int32), inputs.kappa_lognormal(m, 1.0)
+    if kind == "loose":  # vertices of no element
+        coords = np.concatenate([coords, np.ones((3, 3))])
+    dim, nv, ne = coords.shape[1], len(coords), len(elems)
+    print(f"[assembly] plan {kind}: nv={nv} ne={ne}", flush=True)
+    rng = np.random.default_rng(1)
+    fills = [(coords, kappa), (coords + 0.01 * rng.standard_normal(coords.shape), rng.uniform(0.5, 2.0, ne)),
+             (coords, kappa)]
+    e = dev(elems, torch.int32)
+    plan, nnz = C.c_void_p(), C.c_int32(0)
+    check(L.amg_p1_plan_device(dim, nv, ne, e.data_ptr(), C.byref(nnz), None, C.byref(plan)))
+    for xy, k in fills:
+        ref = amg.assemble_p1(xy, elems, k)
+        assert nnz.value == len(ref[1])
+        x, kd = dev(xy, torch.float64), dev(k, torch.float64)
+        out = [torch.full((nv + 1,), -7, dtype=torch.int32, device="cuda"),
+               torch.full((nnz.value,), -7, dtype=torch.int32, device="cuda"),
+               torch.full((nnz.value,), -7.0, dtype=torch.float64, device="cuda"),
+               torch.full((nnz.value,), -7.0, dtype=torch.float64, device="cuda")]
+        torch.cuda.synchronize()
+        check(L.amg_p1_assemble_planned(plan, x.data_ptr(), e.data_ptr(), kd.data_ptr(), *[o.data_ptr() for o in out]))
+        for a, b in zip(out, ref):
+            assert np.array_equal(a.cpu().numpy(), b)
+    assert L.amg_p1_plan_destroy(plan) == 0
+
+
+def test_plan_errors():
+    _need_gpu()
+    from paper_2001_11533_amd._lib import lib
+    L = lib()
+    m = inputs.mesh2d(6)
+    e = dev(m.elems, torch.int32)
+    n = C.c_int32(0)
+
+    def make(dim=2, nv=m.nverts, ne=len(m.elems), elems=e, nnz=n):
+        plan = C.c_void_p(1234)
+        rc = L.amg_p1_plan_device(dim, nv, ne, None if elems is None else elems.data_ptr(),
+                                  None if nnz is None else C.byref(nnz), None, C.byref(plan))
+        return rc, plan
+
+    for kw in ({"dim": 4}, {"nv": 0}, {"ne": 0}, {"elems": None}, {"nnz": None}):
+        rc, plan = make(**kw)
+        assert rc == -1 and plan.value is None, kw
+    for ident in (m.nverts, -1):  # found on the device before any use
+        bad = e.clone()
+        bad[3, 1] = ident
+        rc, plan = make(elems=bad)
+        assert rc == -1 and plan.value is None
+    assert L.amg_p1_plan_device(2, m.nverts, len(m.elems), e.data_ptr(), C.byref(n), None, None) == -1
+    rc, plan = make()
+    assert rc == 0 and plan.value
+    v = torch.zeros(max(n.value, 2 * m.nverts, m.nverts + 1, len(m.elems)), dtype=torch.float64, device="cuda")
+    args = [plan, v.data_ptr(), e.data_ptr(), v.data_ptr(), v.data_ptr(), v.data_ptr(), v.data_ptr(), v.data_ptr()]
+    for k in range(len(args)):
+        assert L.amg_p1_assemble_planned(*[None if i == k else a for i, a in enumerate(args)]) == -1
+    assert bool((v == 0).all())
+    assert L.amg_p1_plan_destroy(plan) == 0
+    assert L.amg_p1_plan_destroy(None) == 0
