@@ -284,3 +284,58 @@ def test_outputs_after_a_failed_inner_solve(nb, mode):
         assert f(g._h, 0, x.data_ptr(), y.data_ptr(), nb, None) == -4
         torch.cuda.synchronize()
         assert bool((y == -7.0).all())
+
+
+# every mass product and its dots on the sliced-ELL copy at every batch width: one
+# slice, a ragged last slice, one and several rounds of eight entries per lane
+@pytest.mark.parametrize("nb", [1, 2, 3, 4, 8, 13, 16])
+@pytest.mark.parametrize("n,offs", [(64, (1, 5, 9)), (127, (1, 5, 9)), (1000, (1, 30, 31)), (5000, range(1, 9))])
+def test_products_and_dots_on_sliced_ell(n, offs, nb):
+    M = stencil(n, offs, n)
+    assert padding(M) <= 1.5
+    mask = (np.random.default_rng(n).random(n) < 0.02).astype(np.uint8)
+    mask[: 2] = [1, 0]
+    g = solver(chain(n), M, mask, nb_max=nb, max_coarse=64)
+    x = np.random.default_rng(nb).standard_normal((n, nb))
+    k = np.diff(M.indptr).max() + 2
+    D = sp.diags(1.0 - mask)
+    for which, op in enumerate([M, D @ M @ D, D @ M, M @ D]):
+        y = g.mass_apply(cuda(x), which).cpu().numpy()
+        assert (np.abs(y - op @ x) <= 2 * k * EPS * (abs(op) @ np.abs(x))).all(), which
+        if which < 2:
+            q = g.mass_quad(cuda(x), which).numpy()
+            mag = np.einsum("ic,ic->c", np.abs(x), abs(op) @ np.abs(x))
+            assert (np.abs(q - np.einsum("ic,ic->c", x, op @ x)) <= 2 * (n + k) * EPS * mag).all(), which
+
+
+# the convergence test ahead of the preconditioner changes neither iterates nor counts:
+# the same solves with captured graphs, which run without it.  One and two columns
+# fold their finalize into the next product here, eight and sixteen do not.
+@pytest.mark.parametrize("n,nb", [(14, 1), (14, 2), (32, 8), (24, 16)])
+@pytest.mark.parametrize("mode", [{}, {"inner_precision": 32}, {"inner_precision": 32, "mixed_mode": 1}])
+@pytest.mark.parametrize("rtol", [1e-2, 1e-9])
+def test_early_convergence_test_is_invisible(n, nb, mode, rtol):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2001_11533_amd as amg
+    p = inputs.config("c3", n=n)
+    rp, ci, va, vm = amg.assemble_p1(p.mesh.coords, p.mesh.elems, p.kappa)
+    rng = np.random.default_rng(n)
+    x, y, z = (p.mesh.coords * np.pi).T
+    u = np.stack([rng.standard_normal(len(x)) if c % 2 else np.sin(x * (c + 1)) * np.sin(y) * np.sin(z)
+                  for c in range(nb)], axis=1)  # smooth and rough columns stop in different iterations
+    if nb > 2:
+        u[:, 2] = 0.0
+    got = []
+    for graphs in (1, 0, 2):
+        g = amg.HessianSolver((rp, ci, va), (rp, ci, vm), p.dirichlet, beta=p.beta, nb_max=nb, inner_rtol=rtol,
+                              max_coarse=40, dense_solve_max=0, use_graphs=graphs, **mode)
+        r = []
+        for v in (u, u[:, ::-1].copy(), u):  # later solves expect what the ones before took
+            y = g.state_solve(cuda(v))
+            r.append((y, g.last_info["inner_iters_total"], g.last_info["inner_iters_max"]))
+        got.append(r)
+    for other in got[1:]:
+        for (a, ia, ma), (b, ib, mb) in zip(got[0], other):
+            assert (ia, ma) == (ib, mb)
+            assert torch.equal(a, b)
