@@ -1798,7 +1798,12 @@ template <> struct Vec16<float> {
 // row, eight (four with four columns) row vectors and theirs in flight per lane
 // (a float32 row of up to 2048 entries is one round).  Every load is
 // unconditional (guarded loads compile to a wait each): vectors past the last
-// that holds an entry re-read it, and entries past n are zeroed in both.  The
+// that holds an entry re-read it, and entries past n are zeroed in both.  In
+// float32 every lane takes part in every round, with nothing but such vectors past
+// the end: a round of at most 16 lanes takes far longer over its conversions to FP64
+// (64 rows or fewer: 3.8, 5.5 and 4.9 us for one, two and four columns, 2.5, 2.7 and
+// 2.6 us with all lanes; 65 rows took that before).  In FP64, without conversions,
+// lanes past the end stay out (600 rows, four columns: 3.3 us, 4.1 with all).  The
 // last vector of b may reach past its entries, within the 16 bytes that hold
 // the last of them.  The stop flag is tested before the store, so no load waits
 // for it, and the few wavefronts per SIMD of such a launch may use the registers
@@ -1810,6 +1815,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) 
     using V = Vec16<TM>;
     using VT = typename V::type;
     constexpr int W = V::n, D = NB < 4 ? 8 : 4;
+    constexpr bool whole = sizeof(TM) == 4;
     const int lane = threadIdx.x % 64;
     const int i = (blockIdx.x * kBlock + threadIdx.x) / 64;
     if (i >= n) return;
@@ -1820,7 +1826,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) 
 #pragma unroll
     for (int c = 0; c < NB; ++c) acc[c] = 0.0;
     const TM *row = inv + (size_t)i * ld;
-    for (int k0 = lane * W; k0 < n; k0 += 64 * W * D) {
+    for (int base = whole ? 0 : lane * W; base < n; base += 64 * W * D) {
+        const int k0 = whole ? base + lane * W : base;
         VT m[D], bv[D][NB];
 #pragma unroll
         for (int u = 0; u < D; ++u) {
