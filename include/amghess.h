@@ -362,7 +362,7 @@ const char *amg_last_error(amg_ctx *ctx);
  * the method's product q = A p: 4 (n+1) + (4 + 8) nnz(A_0) + 2 8 n nb).  Level-0 products
  * run on a sliced-ELL copy whose columns are 16-bit offsets from a base
  * per slice of 64 rows (built when every slice spans fewer than 65536 columns; a
- * batch uses it while its padding is at most half of the stored entries),
+ * batch uses it on large matrices whose padding is at most half of the stored entries),
  * and T_0's columns are kept as 16-bit values when level 1 has at most 65536 nodes
  * (for one column also beyond, as offsets from the place of the row in level 1, where
  * they all fit); such column indices count 2 bytes, all others 4.

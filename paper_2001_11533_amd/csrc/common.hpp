@@ -195,10 +195,22 @@ struct DCsr {
     uint16_t *sl_cd = nullptr;
     double *sl_v = nullptr;
     float *sl_v32 = nullptr;
-    // whether products on nb columns run on the copy: always for one column; a
-    // batch, whose gathers and multiplications for a padded entry cost as much as
-    // for a stored one, only up to half as many again (3D P1 rows pad by 12 %)
-    bool sell_for(int nb) const { return sl_off && (nb == 1 || 2 * sl_tot <= 3L * nnz); }
+    // whether products on nb columns run on the copy: always for one column.  A batch
+    // pays for a padded entry's gathers and multiplications as for a stored one's: only
+    // up to half as many again (3D P1 rows pad by 12 %).  And it needs rows enough: a
+    // lane takes a whole row (of up to four columns), in rounds of eight entries, while
+    // the CSR product spreads a small matrix over 2^17 lanes.  Rows of up to eight
+    // entries take the copy from 2^15 lanes on (the three level-0 passes of a FP64
+    // Chebyshev cycle on 7-point rows, copy / CSR in us: 29791 rows x 4 11.2 / 10.0,
+    // 39304 x 4 11.3 / 12.2, 12167 x 8 10.9 / 10.0, 29791 x 8 11.6 / 12.6, 6859 x 16
+    // 11.3 / 10.1, 12167 x 16 11.2 / 12.2), longer ones, two rounds, from 2^16 rows on
+    // (15-point mass rows: 1728 x 8 6.3 / 4.0, 39304 x 2 5.4 / 4.4, 39304 x 8 8.8 / 7.7,
+    // 91125 x 4 9.0 / 10.9, 91125 x 8 12.2 / 13.2).
+    bool sell_for(int nb) const {
+        if (!sl_off || nb == 1) return sl_off != nullptr;
+        const bool rows_enough = nnz <= 8L * n ? (long)n * (nb > 4 ? nb / 4 : 1) >= 1L << 15 : n >= 1 << 16;
+        return rows_enough && 2 * sl_tot <= 3L * nnz;
+    }
     // optional 16-bit columns of a large coarse matrix for products on one column:
     // entry p of row i is column row_base(i, c16_scale) + c16[p] (present only when
     // every offset fits)

@@ -226,12 +226,13 @@ def padding(M):
 
 # a value that is not finite reaches the rows that hold its node and no others,
 # whatever entries a matrix copy pads its rows with: single values at the smallest
-# column of a slice of 64 rows.  Rows of at most eight and of more entries in sliced
-# ELL at every width, a few long rows on CSR for batches
+# column of a slice of 64 rows.  Rows of at most eight and of more entries, on CSR and
+# (one column always, batches from 2^15 lanes or 2^16 long rows on) in sliced ELL; a
+# few long rows, on CSR for batches
 @pytest.mark.parametrize("nb", [1, 2, 3, 4, 8, 16])
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
 @pytest.mark.parametrize("n,offs", [(64, (1, 5, 9)), (127, (1, 5, 9)), (1000, (1, 30, 31)), (5000, range(1, 9)),
-                                    (3001, None)])
+                                    (3001, None), (33001, (1, 30, 31)), (65601, range(1, 9))])
 def test_products_keep_non_finite_values_to_their_rows(n, offs, bad, nb):
     if offs:
         M = stencil(n, offs, n)
@@ -286,10 +287,14 @@ def test_outputs_after_a_failed_inner_solve(nb, mode):
         assert bool((y == -7.0).all())
 
 
-# every mass product and its dots on the sliced-ELL copy at every batch width: one
-# slice, a ragged last slice, one and several rounds of eight entries per lane
+# every mass product and its dots on matrices that pad by little: around the rows from
+# which a batch runs on the sliced-ELL copy (2^13, 2^14 and 2^15 at 16, 8 and up to four
+# columns; 2^16 where rows are longer than eight entries), one slice, ragged last
+# slices, one and several rounds of eight entries per lane
 @pytest.mark.parametrize("nb", [1, 2, 3, 4, 8, 13, 16])
-@pytest.mark.parametrize("n,offs", [(64, (1, 5, 9)), (127, (1, 5, 9)), (1000, (1, 30, 31)), (5000, range(1, 9))])
+@pytest.mark.parametrize("n,offs", [(64, (1, 5, 9)), (127, (1, 5, 9)), (1000, (1, 30, 31)), (5000, range(1, 9)),
+                                    (8191, (1, 30, 31)), (8193, (1, 30, 31)), (16385, (1, 30, 31)),
+                                    (32769, (1, 30, 31)), (65535, range(1, 9)), (65601, range(1, 9))])
 def test_products_and_dots_on_sliced_ell(n, offs, nb):
     M = stencil(n, offs, n)
     assert padding(M) <= 1.5
