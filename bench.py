@@ -505,7 +505,10 @@ def main():
         "roofline": dict(rooflines[DOMINANT], dominant=("largest summed device time in the headline solve's "
                                                         "kernel trace (profiles/solve_c3_kernel_trace.txt)")),
         "roofline_others": {k: v for k, v in rooflines.items() if k != DOMINANT},
-        "roofline_128cube": dict(big, note="the same kernels on the 128^3 level-0 matrix, algorithmic bytes"),
+        "roofline_128cube": dict(big, note=("the same kernels on the 128^3 level-0 matrix, algorithmic bytes; launched "
+                                            "back to back, the matrix and vectors of a pass (112 to 218 MB) stay "
+                                            "largely in the 256 MB Infinity Cache, so frac is no share of what HBM "
+                                            "alone delivers")),
         "grid_sync_us": {"cooperative_grid_barrier": bar_ms * 1e3, "kernel_boundary": bnd_ms * 1e3,
                          "note": ("one workgroup per CU, an elementwise step over 2^16 floats per round; "
                                   "barrier = release fence, arrival counter, generation flag, acquire fence")},
